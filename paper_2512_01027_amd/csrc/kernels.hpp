@@ -220,23 +220,23 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(PULBM_GLB char* base,
 {
     return __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000);
 }
-template <bool NT, class T> __device__ __forceinline__ T buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t boff)
+template <bool NT, class T> __device__ __forceinline__ T buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t boff, uint32_t soff)
 {
     constexpr int aux = NT ? 2 : 0;
-    if constexpr (sizeof(T) == 2) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, (int)boff, 0, aux));
-    else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)boff, 0, aux));
-    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)boff, 0, aux));
+    if constexpr (sizeof(T) == 2) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, (int)boff, (int)soff, aux));
+    else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)boff, (int)soff, aux));
+    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)boff, (int)soff, aux));
 }
-template <bool NT, class T> __device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, uint32_t boff, T v)
+template <bool NT, class T> __device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, uint32_t boff, uint32_t soff, T v)
 {
     constexpr int aux = NT ? 2 : 0;
     if constexpr (sizeof(T) == 2) {
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, (int)boff, 0, aux);
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, (int)boff, (int)soff, aux);
     } else if constexpr (sizeof(T) == 4) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, (int)boff, 0, aux);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, (int)boff, (int)soff, aux);
     } else {
         typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)boff, 0, aux);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)boff, (int)soff, aux);
     }
 }
 
@@ -248,10 +248,15 @@ struct Slots {
     {
         return (PULBM_GLB T*)(base + (uint64_t)slot * slot_bytes + boff);
     }
+    // One resource serves the two slots of an opposite pair (2 slot_bytes stay
+    // below 2^32), the second at a scalar offset: a resource takes four SGPRs,
+    // and one per slot kept more of them live than there are.
+    __device__ static __forceinline__ int pair(int slot) { return slot == 0 ? 0 : ((slot - 1) | 1); }
     __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(int slot) const
     {
-        return buf_rsrc(base + (uint64_t)slot * slot_bytes, (uint32_t)slot_bytes);
+        return buf_rsrc(base + (uint64_t)pair(slot) * slot_bytes, 2u * (uint32_t)slot_bytes);
     }
+    __device__ __forceinline__ uint32_t soff(int slot) const { return slot == pair(slot) ? 0u : (uint32_t)slot_bytes; }
 };
 
 template <class T> __device__ __forceinline__ Slots<T> slots(void* p, int64_t N)
@@ -267,12 +272,12 @@ template <class T> __device__ __forceinline__ Slots<T> slots(void* p, int64_t N)
 // each component is encoded with g's codec and scale (no shift) and two of
 // them share a 32-bit word (word j holds components 2j and 2j + 1, the first
 // in the low half), so a node's six values take three loads and three
-// registers.
-template <class S> __device__ __forceinline__ uint32_t m2_pack(S lo, S hi)
+// registers.  The collide keeps 2-byte h in registers the same way.
+template <class S> __device__ __forceinline__ uint32_t pair_pack(S lo, S hi)
 {
     return (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
 }
-template <class S> __device__ __forceinline__ S m2_half(uint32_t w, int k)
+template <class S> __device__ __forceinline__ S pair_half(uint32_t w, int k)
 {
     return __builtin_bit_cast(S, (uint16_t)(k ? w >> 16 : w & 0xffffu));
 }
@@ -420,9 +425,9 @@ template <class S, int A> constexpr bool nt_access() { return ((sizeof(S) >= 4 ?
 template <class L, bool WALL, bool NT, class S>
 __device__ __forceinline__ S aa_load(const Slots<S>& f, uint32_t nb, const Nav& v, int i, bool odd)
 {
-    if (!odd) return buf_ld<NT, S>(f.rsrc(i), nb);
-    if (WALL && nav_solid<L>(v, i, -1)) return buf_ld<NT, S>(f.rsrc(i), nb);  // reflected at a wall last step
-    return buf_ld<NT, S>(f.rsrc(opp(i)), nb + (uint32_t)nav_off<L>(v, i, -1));
+    if (!odd) return buf_ld<NT, S>(f.rsrc(i), nb, f.soff(i));
+    if (WALL && nav_solid<L>(v, i, -1)) return buf_ld<NT, S>(f.rsrc(i), nb, f.soff(i));  // reflected at a wall last step
+    return buf_ld<NT, S>(f.rsrc(opp(i)), nb + (uint32_t)nav_off<L>(v, i, -1), f.soff(opp(i)));
 }
 
 // Store the node's post-collision population i where it streams to; a
@@ -432,8 +437,8 @@ template <class L, bool WALL, bool NT, class S>
 __device__ __forceinline__ void aa_store(const Slots<S>& f, uint32_t nb, const Nav& v, int i, bool odd, S val,
                                          bool bb)
 {
-    if (!odd || (WALL && bb)) buf_st<NT, S>(f.rsrc(opp(i)), nb, val);
-    else buf_st<NT, S>(f.rsrc(i), nb + (uint32_t)nav_off<L>(v, i, +1), val);
+    if (!odd || (WALL && bb)) buf_st<NT, S>(f.rsrc(opp(i)), nb, f.soff(opp(i)), val);
+    else buf_st<NT, S>(f.rsrc(i), nb + (uint32_t)nav_off<L>(v, i, +1), f.soff(i), val);
 }
 
 // ---------------------------------------------------------- tile regions
@@ -469,6 +474,58 @@ struct Region {
     __device__ static __forceinline__ int nb_base(int cx, int cy, int cz) { return idx(cx - 1, cy - 1, cz - ZL); }
     template <int ZL>
     static constexpr int nb(int dx, int dy, int dz) { return (1 + dx) + RX * ((1 + dy) + RY * (ZL + dz)); }
+};
+
+// The stencil fields of a tile's cells in LDS: NF values to a cell, in 16-byte
+// words (one ds_read_b128 brings four FP32 or two FP64 values of a neighbour)
+// and, where NF is odd, one value apart.  Each word array has a 16-byte pitch,
+// so a wavefront's row is read without bank conflicts.
+template <class CT, int NF, int NC> struct Cells {
+    static constexpr int PW = 16 / (int)sizeof(CT), NW = NF / PW, REM = NF % PW;
+    static_assert(REM <= 1, "at most one value apart");
+    typedef CT V __attribute__((ext_vector_type(PW)));
+    V w[NW][NC];
+    CT r[REM ? NC : 1];
+    // A cell that neighbours are read from at constant offsets: its byte
+    // offset in each array, hidden from the compiler's bit tracking so that
+    // every read takes its offset as an immediate from one register per pitch.
+    // (Left visible, each row of the 3x3x3 block gets an address of its own,
+    // formed from the bits of the thread index and kept live.)
+    struct At {
+        int bw, br;
+        __device__ __forceinline__ void hide()
+        {
+            asm volatile("" : "+v"(bw));
+            asm volatile("" : "+v"(br));
+        }
+    };
+    __device__ static __forceinline__ At at(int k)
+    {
+        At a = {k * 16, k * (int)sizeof(CT)};
+        a.hide();
+        return a;
+    }
+    __device__ __forceinline__ void get(At at, int off, CT* f) const
+    {
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            const V v = *(const V*)((const char*)&w[j][off] + at.bw);
+#pragma unroll
+            for (int c = 0; c < PW; ++c) f[j * PW + c] = v[c];
+        }
+        if constexpr (REM != 0) f[NF - 1] = *(const CT*)((const char*)&r[off] + at.br);
+    }
+    __device__ __forceinline__ void put(int k, const CT* f)
+    {
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            V v;
+#pragma unroll
+            for (int c = 0; c < PW; ++c) v[c] = f[j * PW + c];
+            w[j][k] = v;
+        }
+        if constexpr (REM != 0) r[k] = f[NF - 1];
+    }
 };
 
 // 1-halo region of a tile: cell k -> mirror node index, wall offsets, crossings.
@@ -554,7 +611,7 @@ struct Halo2 {
 // open end is the mirror row (resolve_axis, with the row's offsets and
 // crossings), and so is an end cell beyond a wall in x; the cells within a
 // row share the row's y and z resolution.
-template <class HR, bool WALL, int NV, class CT, class StoreF>
+template <class HR, bool WALL, int NV, class CT, bool FENCE, class StoreF>
 __device__ __forceinline__ void halo_rows(CDesc& cs, const TileCtx& t, void* const* src, StoreF store)
 {
     using R = typename HR::R;
@@ -617,6 +674,7 @@ __device__ __forceinline__ void halo_rows(CDesc& cs, const TileCtx& t, void* con
 #pragma unroll
         for (int j = 0; j < NV; ++j) e[p][j] = *at_node<CT>(src[j], row + (uint32_t)x);
     }
+    if constexpr (FENCE) __builtin_amdgcn_sched_barrier(0);  // every load issued, then the LDS writes
 #pragma unroll
     for (int p = 0; p < PV; ++p)
 #pragma unroll
@@ -640,16 +698,16 @@ __device__ __forceinline__ bool halo_near_block(CDesc& cs, const TileCtx& t)
            t.oz + TZ + HR::ZH > cs.blk_lo[2];
 }
 
-template <class HR, bool WALL, int NV, class CT, class StoreF>
+template <class HR, bool WALL, int NV, class CT, bool FENCE = false, class StoreF>
 __device__ __forceinline__ void halo_stage(CDesc& cs, const TileCtx& t, void* const* src, StoreF store)
 {
     if (t.ox + HR::RX - 2 * HR::D <= cs.nx) {
         if constexpr (!WALL) {
-            halo_rows<HR, false, NV, CT>(cs, t, src, store);
+            halo_rows<HR, false, NV, CT, FENCE>(cs, t, src, store);
             return;
         } else {
             if (!halo_near_block<HR>(cs, t)) {
-                halo_rows<HR, true, NV, CT>(cs, t, src, store);
+                halo_rows<HR, true, NV, CT, FENCE>(cs, t, src, store);
                 return;
             }
         }
@@ -674,6 +732,8 @@ __device__ __forceinline__ void halo_stage(CDesc& cs, const TileCtx& t, void* co
 template <class CT> __device__ __forceinline__ CT rcp(CT x) { return (CT)1 / x; }
 template <> __device__ __forceinline__ float rcp<float>(float x) { return __builtin_amdgcn_rcpf(x); }
 template <class CT> __device__ __forceinline__ CT sqrt_(CT x) { return sqrt(x); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <> __device__ __forceinline__ float sqrt_<float>(float x) { return __builtin_amdgcn_sqrtf(x); }
 
 template <class CT>
@@ -719,7 +779,10 @@ template <class CT> __device__ __forceinline__ CT clamp01(CT v) { return v < (CT
 // Local macroscopic values and gradients of one node.
 template <class CT>
 struct NodeVals {
-    CT phi, u[3], gphi[3], lphi, grho[3], G[3][3];  // G[a][b] = d u_a / d x_b
+    CT phi, u[3], gphi[3], lphi, grho[3];
+    // of the velocity gradients G_ab = d u_a / d x_b: div u, 2 G_aa, and
+    // G_01 + G_10, G_02 + G_20, G_12 + G_21
+    CT div, G2[3], Gs[3];
 };
 
 // Macroscopic part of the collision of one node (everything but the
@@ -779,9 +842,7 @@ __device__ __forceinline__ NodeCoef<DIMV, CT> node_coef(const Phys<CT>& p, const
     k.rho = rho;
 #pragma unroll
     for (int a = 0; a < 3; ++a) k.F[a] = a < D ? rho * p.grav[a] + mu * v.gphi[a] : (CT)0;
-    CT div = v.G[0][0];
-#pragma unroll
-    for (int a = 1; a < D; ++a) div += v.G[a][a];
+    const CT div = v.div;
     const CT bulk = rho * (CT)(2.0 / 3.0) * (p.lambda_b - nu) * div;
     const CT rnu = rho * nu;
 #pragma unroll
@@ -790,7 +851,7 @@ __device__ __forceinline__ NodeCoef<DIMV, CT> node_coef(const Phys<CT>& p, const
         CT sg = 0;
 #pragma unroll
         for (int m = 0; m < D; ++m) {
-            CT s_lm = rnu * (v.G[l][m] + v.G[m][l]);
+            CT s_lm = rnu * (l == m ? v.G2[l] : v.Gs[l + m - 1]);
             if (l == m) s_lm += bulk;
             sg += s_lm * v.grho[m];
         }
@@ -925,32 +986,6 @@ __device__ __forceinline__ void g_pair(const NodeVals<CT>& v, const NodeCoef<D, 
     *ok = we - ca * w3;
 }
 
-// Isotropic central differences (Sec. II) of a tile field at cell (cx,cy,cz):
-// grad_a q = sum_i w_i c_ia (q(+c_i) - q(-c_i)) / (2T), lap q = 2 sum_i w_i (q(+c_i) - q0) / T.
-template <class G, class RG, class CT, class F>
-__device__ __forceinline__ void stencil(F q, int cx, int cy, int cz, CT grad[3], CT* lap)
-{
-    CT gr[3] = {0, 0, 0};
-    CT l = 0;
-    const CT q0 = q(RG::idx(cx, cy, cz));
-#pragma unroll
-    for (int i = 1; i < G::Q; i += 2) {  // pairs (i, i+1) are opposite
-        const CT qp = q(RG::idx(cx + G::c(i, 0), cy + G::c(i, 1), cz + G::c(i, 2)));
-        const CT qm = q(RG::idx(cx - G::c(i, 0), cy - G::c(i, 1), cz - G::c(i, 2)));
-        const CT d = (qp - qm) * (CT)G::w(i);
-#pragma unroll
-        for (int a = 0; a < G::DIM; ++a) {
-            if (G::c(i, a) == 1) gr[a] += d;
-            if (G::c(i, a) == -1) gr[a] -= d;
-        }
-        if (lap) l += (qp + qm - (CT)2 * q0) * (CT)G::w(i);
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) grad[a] = gr[a] * (CT)3.0;  // 2 * (1/(2T)): each pair counted once
-    if (lap) *lap = l * (CT)6.0;                             // 2/T
-}
-
-
 template <class Mo>
 __device__ __forceinline__ void local_xyz(int* lx, int* ly, int* lz)
 {
@@ -1068,7 +1103,7 @@ __device__ __forceinline__ void moments_node(CDesc& cs, int x, int y, int z, boo
         for (int j = 0; j < (NM + 1) / 2; ++j) {
             const S lo = Codec<S>::enc(m2[2 * j], gsc_out, (CT)0);
             const S hi = 2 * j + 1 < NM ? Codec<S>::enc(m2[2 * j + 1], gsc_out, (CT)0) : (S)0;
-            __builtin_nontemporal_store(m2_pack<S>(lo, hi), Ms.at(j, n * 4u));
+            __builtin_nontemporal_store(pair_pack<S>(lo, hi), Ms.at(j, n * 4u));
         }
     } else {
         const Slots<CT> Ms = slots<CT>(cs.M2, cs.N);
@@ -1326,36 +1361,120 @@ __global__ __launch_bounds__(256) void k_velocity(CaseTab cases, const int* hdr,
     else velocity_tile<LS, CT, false, R>(cs, t, sP, sGD);
 }
 
-// Gradients of phi, rho and u at interior cell (cx, cy, cz) of a 1-halo tile.
-template <int LS, class R, class CT>
-__device__ __forceinline__ void tile_gradients(const CT* sPhi, const CT* sRho, const CT (*sU)[R::N], int cx,
-                                               int cy, int cz, NodeVals<CT>& v)
+// Fields of a cell of the collide and init tiles, in LDS order: phi, u, rho.
+template <int DIMV> struct CellF {
+    static constexpr int NF = DIMV + 2, PHI = 0, U = 1, RHO = DIMV + 1;
+};
+
+// Rounding of the gradient sums, written out so that a kernel's results do
+// not depend on where the compiler places a product: it contracts a product
+// into the sum only within one basic block, and the run-time parity and the
+// BF16 codec split the collide into several.
+// Which velocity-gradient terms add a product rounded on its own instead of
+// contracting it (SPLIT 0: none, 1: d u_y / dz and d u_z / dy, 2: every
+// off-diagonal component): terms of d u_a / d x_b along a direction i whose
+// product another component takes first.
+template <class G, int SPLIT> __host__ __device__ constexpr bool grad_split(int i, int a, int b)
+{
+    if (SPLIT == 0 || a < 0 || a >= G::DIM || a == b || G::c(i, b) == 0) return false;
+    if (a > 0 && b > 0) return G::c(i, a) != 0 || G::c(i, 0) != 0;
+    return SPLIT == 2 && G::c(i, a) != 0;
+}
+template <class S, bool WALL, bool BGK, int PAR> constexpr int grad_split_of()
+{
+    if (std::is_same_v<S, uint16_t>) return 2;
+    return PAR == 1 && WALL ? (BGK ? 2 : 1) : 0;
+}
+
+// Isotropic central differences (Sec. II) of phi, rho and u at the cell whose
+// 3x3(x3) neighbourhood starts at cell kb (R::nb_base):
+// grad_a q = sum_i w_i c_ia (q(+c_i) - q(-c_i)) / (2T), lap q = 2 sum_i w_i (q(+c_i) - q0) / T.
+template <int LS, class R, int ZH, int SPLIT, class C, class CT>
+__device__ __forceinline__ void tile_gradients(const C& cells, typename C::At kb, NodeVals<CT>& v)
 {
     constexpr int DIMV = Model<LS>::DIM;
     using G = typename Model<LS>::G;
-    const int c0 = R::idx(cx, cy, cz);
-    v.phi = sPhi[c0];
+    using F = CellF<DIMV>;
+    CT q0[F::NF];
+    cells.get(kb, R::template nb<ZH>(0, 0, 0), q0);
+    v.phi = q0[F::PHI];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) v.u[a] = a < DIMV ? sU[a][c0] : (CT)0;
-    stencil<G, R, CT>([&](int k) { return sPhi[k]; }, cx, cy, cz, v.gphi, &v.lphi);
-    stencil<G, R, CT>([&](int k) { return sRho[k]; }, cx, cy, cz, v.grho, (CT*)nullptr);
+    for (int a = 0; a < 3; ++a) v.u[a] = a < DIMV ? q0[F::U + a] : (CT)0;
+    CT gr[F::NF][3], l = 0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+    for (int f = 0; f < F::NF; ++f) gr[f][0] = gr[f][1] = gr[f][2] = 0;
+    // The reads of a pair are issued AHEAD pairs before its sums, and no
+    // sooner: the sums are pinned in order and the reads' address depends on
+    // the last pin.  Left to itself the compiler issues all 26 neighbours'
+    // reads first, which alone takes 130 registers (the D3Q27 collide then
+    // needs 153-168; with 2 pairs ahead 83 on even and 115 on odd steps; 1 pair
+    // ahead is 1-5% slower, 3 and more no faster).
+    constexpr int AHEAD = 2, NP = G::Q / 2;
+    CT qp[AHEAD][F::NF], qm[AHEAD][F::NF];
+    auto read = [&](int n) {
+        const int i = 2 * n + 1;
+        cells.get(kb, R::template nb<ZH>(G::c(i, 0), G::c(i, 1), G::c(i, 2)), qp[n % AHEAD]);
+        cells.get(kb, R::template nb<ZH>(-G::c(i, 0), -G::c(i, 1), -G::c(i, 2)), qm[n % AHEAD]);
+    };
 #pragma unroll
-        for (int b = 0; b < 3; ++b) v.G[a][b] = 0;
+    for (int n = 0; n < AHEAD; ++n) read(n);
 #pragma unroll
-    for (int a = 0; a < DIMV; ++a) {
-        CT gr[3];
-        stencil<G, R, CT>([&](int k) { return sU[a][k]; }, cx, cy, cz, gr, (CT*)nullptr);
+    for (int n = 0; n < NP; ++n) {
+        const int i = 2 * n + 1;  // the opposite directions i and i + 1
+        const CT* p = qp[n % AHEAD];
+        const CT* m = qm[n % AHEAD];
 #pragma unroll
-        for (int b = 0; b < DIMV; ++b) v.G[a][b] = gr[b];
+        for (int f = 0; f < F::NF; ++f) {
+            const CT s = p[f] - m[f], d = s * (CT)G::w(i);
+#pragma unroll
+            for (int a = 0; a < DIMV; ++a) {
+                if (grad_split<G, SPLIT>(i, f - F::U, a)) {
+                    CT r = s * (CT)G::w(i);
+                    asm("" : "+v"(r));
+                    if (G::c(i, a) == 1) gr[f][a] += r;
+                    if (G::c(i, a) == -1) gr[f][a] -= r;
+                } else {
+                    if (G::c(i, a) == 1) gr[f][a] += d;
+                    if (G::c(i, a) == -1) gr[f][a] -= d;
+                }
+            }
+        }
+        l += (p[F::PHI] + m[F::PHI] - (CT)2 * q0[F::PHI]) * (CT)G::w(i);
+#pragma unroll
+        for (int f = 0; f < F::NF; ++f)
+#pragma unroll
+            for (int a = 0; a < DIMV; ++a)
+                if (G::c(i, a) != 0) asm volatile("" : "+v"(gr[f][a]));
+        asm volatile("" : "+v"(l));
+        kb.hide();
+        if (n + AHEAD < NP) read(n + AHEAD);
     }
+    // 2 * (1/(2T)): each pair counted once
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        v.gphi[a] = gr[F::PHI][a] * (CT)3.0;
+        v.grho[a] = gr[F::RHO][a] * (CT)3.0;
+        v.G2[a] = a < DIMV ? gr[F::U + (a < DIMV ? a : 0)][a] * (CT)6.0 : (CT)0;
+        v.Gs[a] = 0;
+    }
+    // the sums the collision takes of the velocity gradients, each rounding
+    // its second term alone (written out, so that every kernel rounds alike)
+    const CT(*gu)[3] = gr + F::U;
+    v.div = SPLIT == 1 ? fma_((CT)3.0, gu[1][1], gu[0][0] * (CT)3.0) : fma_((CT)3.0, gu[0][0], gu[1][1] * (CT)3.0);
+    v.Gs[0] = fma_((CT)3.0, gu[0][1], gu[1][0] * (CT)3.0);
+    if constexpr (DIMV == 3) {
+        v.div = fma_((CT)3.0, gu[2][2], v.div);
+        v.Gs[1] = fma_((CT)3.0, gu[0][2], gu[2][0] * (CT)3.0);
+        v.Gs[2] = fma_((CT)3.0, gu[1][2], gu[2][1] * (CT)3.0);
+    }
+    v.lphi = l * (CT)6.0;  // 2/T
 }
 
 // --- collide + stream.  A tile first issues the loads of its own nodes'
-// incoming h (parked in LDS until the direction loop) and M2,
-// together with the halo loads of phi and u, so that their latencies overlap;
-// then it takes the gradients from LDS and collides one direction at a time.
+// incoming h and M2 together with the halo loads of phi and u, so that their
+// latencies overlap (h then waits in registers, two to each, in 2-byte storage
+// and in LDS otherwise); then it takes the gradients from LDS and collides one
+// direction at a time.
 // The tile's step read again from the descriptor (a volatile load, so the
 // compiler cannot take it for the value a branch already tested).
 __device__ __forceinline__ int64_t step_parity(CDesc& cs, const TileCtx& t)
@@ -1363,10 +1482,14 @@ __device__ __forceinline__ int64_t step_parity(CDesc& cs, const TileCtx& t)
     return *(const volatile PULBM_CST int64_t*)&cs.step + (t.step - cs.step);
 }
 
+template <int LS, class S>
+using TileCells = Cells<typename Codec<S>::CT, CellF<Model<LS>::DIM>::NF, Halo1<Model<LS>, Model<LS>::DIM>::R::N>;
+
+// Does a lattice set's collide kernel rebuild u for some cases (CaseDev::fuse_u)?
+template <int LS, class S> constexpr bool can_fuse_u() { return LS != 3 && sizeof(S) >= 4; }
+
 template <int LS, class S, bool WALL, bool BGK, class R, int PAR>
-__device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typename Codec<S>::CT* sPhi,
-                                             typename Codec<S>::CT* sRho,
-                                             typename Codec<S>::CT (*sU)[R::N], S (*sH)[256],
+__device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCells<LS, S>& sC, S (*sH)[256],
                                              typename Codec<S>::CT* sP2)
 {
     constexpr int DIMV = Model<LS>::DIM;
@@ -1375,6 +1498,7 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typena
     using H = typename Mo::H;
     using CT = typename Codec<S>::CT;
     using HR = Halo1<Mo, DIMV>;
+    using F = CellF<DIMV>;
     constexpr int NM = DIMV == 2 ? 3 : 6;
     const Phys<CT> ph = make_phys<CT>(cs);
     int lx, ly, lz;
@@ -1409,7 +1533,7 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typena
     CT php = 0;  // reference of the incoming h (2-byte storage)
     CT dP = 0;   // BGK: (previous P - new P) / (rho_ref T), restores the stored rest population
     CT ur[3] = {0, 0, 0};  // BGK, 2-byte storage: reference of the incoming g
-    if (inside) {
+    {
         php = h_reference<S>(cs.phi[(t.step + 1) & 1], n);
         if constexpr (BGK) u_reference<S, DIMV>(cs.U[(t.step + 1) & 1], cs.N, n, ur);
 #pragma unroll
@@ -1417,53 +1541,57 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typena
         if constexpr (BGK) {
             dP = (CT)(((double)*at_node<CT>(cs.P[t.step & 1], n) - (double)*at_node<CT>(cs.P[(t.step + 1) & 1], n)) *
                       (3.0 / cs.rho_a));
+            asm("" : "+v"(dP));
         } else {
             const Slots<M2L> Ms = slots<M2L>(cs.M2, cs.N);
 #pragma unroll
             for (int k = 0; k < NL; ++k) m2l[k] = __builtin_nontemporal_load(Ms.at(k, na));
         }
     }
-    // 2-byte storage parks h in LDS before the halo loads: the codec's extra
-    // registers leave no room to hold h and every halo value at once
-    if constexpr (sizeof(S) == 2) {
-        if (inside) {
-#pragma unroll
-            for (int j = 0; j < H::Q; ++j) sH[j][threadIdx.x] = hraw[j];
-        }
-    }
+    __builtin_amdgcn_sched_barrier(0);  // the own-node loads are issued first
     // halo of phi, rho and u; a fused case (no wall, open end or block)
     // loads u* instead of u and the new P two nodes deep, and rebuilds u
     // itself below
     bool fused = false;
-    if constexpr (!WALL && sizeof(S) >= 4) fused = cs.fuse_u;
+    if constexpr (!WALL && can_fuse_u<LS, S>()) fused = cs.fuse_u;
     const Slots<CT> Us = slots<CT>(fused ? cs.J : cs.U[t.step & 1], cs.N);
     void* src[1 + DIMV];
     src[0] = cs.phi[t.step & 1];
 #pragma unroll
     for (int a = 0; a < DIMV; ++a) src[1 + a] = (void*)Us.at(a, 0);
-    halo_stage<HR, WALL, 1 + DIMV, CT>(
+    halo_stage<HR, WALL, 1 + DIMV, CT, true>(
         cs, t, src,
         [&](int k, int cr, const int*, const CT* v) {
-            sPhi[k] = v[0];
-            sRho[k] = ph.rho_a + clamp01(v[0]) * ph.drho;
+            CT f[F::NF];
+            f[F::PHI] = v[0];
+            f[F::RHO] = ph.rho_a + clamp01(v[0]) * ph.drho;
 #pragma unroll
-            for (int a = 0; a < DIMV; ++a) sU[a][k] = (WALL && (cr & 1)) ? -v[1 + a] : v[1 + a];  // no slip
+            for (int a = 0; a < DIMV; ++a) f[F::U + a] = (WALL && (cr & 1)) ? -v[1 + a] : v[1 + a];  // no slip
+            sC.put(k, f);
         });
-    if constexpr (!WALL && sizeof(S) >= 4) {
+    if constexpr (!WALL && can_fuse_u<LS, S>()) {
         if (fused) {
             void* psrc[1] = {cs.P[(t.step + 1) & 1]};
             halo_stage<Halo2<Mo, DIMV>, false, 1, CT>(cs, t, psrc,
                                                       [&](int k, int, const int*, const CT* v) { sP2[k] = v[0]; });
         }
     }
-    if constexpr (sizeof(S) != 2) {
-        if (inside) {
+    // 4- and 8-byte storage parks h in LDS until the direction loop; 2-byte
+    // storage keeps it in registers, two values to each
+    uint32_t h2[(H::Q + 1) / 2];
+    if constexpr (sizeof(S) == 2) {
 #pragma unroll
-            for (int j = 0; j < H::Q; ++j) sH[j][threadIdx.x] = hraw[j];
-        }
+        for (int j = 0; j < H::Q; j += 2) h2[j / 2] = pair_pack<S>(hraw[j], j + 1 < H::Q ? hraw[j + 1] : (S)0);
+    } else {
+#pragma unroll
+        for (int j = 0; j < H::Q; ++j) sH[j][threadIdx.x] = hraw[j];
     }
+    auto h_in = [&](int j) -> S {
+        if constexpr (sizeof(S) == 2) return pair_half<S>(h2[j / 2], j & 1);
+        else return sH[j][threadIdx.x];
+    };
     __syncthreads();
-    if constexpr (!WALL && sizeof(S) >= 4) {
+    if constexpr (!WALL && can_fuse_u<LS, S>()) {
         if (fused) {
             // u = u* - D P / rho at every cell of the 1-halo region, the
             // expression of k_velocity term by term
@@ -1487,9 +1615,12 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typena
                             if (G::c(i, a) == -1) gr[a] -= d;
                         }
                     }
-                    const CT irho = rcp(sRho[k]);
+                    CT f[F::NF];
+                    sC.get({k * 16, k * (int)sizeof(CT)}, 0, f);
+                    const CT irho = rcp(f[F::RHO]);
 #pragma unroll
-                    for (int a = 0; a < DIMV; ++a) sU[a][k] = sU[a][k] - gr[a] * (CT)3.0 * irho;
+                    for (int a = 0; a < DIMV; ++a) f[F::U + a] = f[F::U + a] - gr[a] * (CT)3.0 * irho;
+                    sC.put(k, f);
                 }
             }
             __syncthreads();
@@ -1502,14 +1633,16 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typena
         if constexpr (sizeof(S) == 2) {
             const CT gsc_m = cconst<CT>(cs.g_inv_scale, cs.f32.g_inv_scale);
 #pragma unroll
-            for (int k = 0; k < NM; ++k) m2[k] = Codec<S>::dec(m2_half<S>(m2l[k / 2], k & 1), gsc_m, (CT)0);
+            for (int k = 0; k < NM; ++k) m2[k] = Codec<S>::dec(pair_half<S>(m2l[k / 2], k & 1), gsc_m, (CT)0);
         } else {
 #pragma unroll
             for (int k = 0; k < NM; ++k) m2[k] = m2l[k];
         }
     }
     NodeVals<CT> v;
-    tile_gradients<LS, R, CT>(sPhi, sRho, sU, lx + 1, ly + 1, lz + HR::ZH, v);
+    const int k0 = R::template nb_base<HR::ZH>(lx + 1, ly + 1, lz + HR::ZH);
+    auto kb = sC.at(k0);
+    tile_gradients<LS, R, HR::ZH, grad_split_of<S, WALL, BGK, PAR>()>(sC, kb, v);
     // the BGK collision needs the equilibria alone (no Pi: the INIT form)
     const NodeCoef<DIMV, CT> kc = node_coef<DIMV, BGK, CT>(ph, v, m2);
     const CT omf = BGK ? (CT)1 - rcp(ph.tau_a + clamp01(v.phi) * ph.dtau) : (CT)0;  // 1 - 1/tau_mix
@@ -1520,17 +1653,21 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typena
     // (this step) of the node that reads it next step: x + c_i, or x itself
     // for a population reflected at a wall, which that node reads as moving
     // along -c_i
-    const int cx = lx + 1, cy = ly + 1, cz = lz + HR::ZH, c0 = R::idx(cx, cy, cz);
-    // (each taken where it is used, which keeps the register budget)
+    // (each read again where it is used, which keeps the register budget:
+    // merged with the gradients' reads they would stay live to the end)
+    __builtin_amdgcn_sched_barrier(0);
+    const auto kd = sC.at(k0);
+    constexpr int c0 = R::template nb<HR::ZH>(0, 0, 0);
     auto gref_out = [&](int i, bool reflected) -> CT {
         if constexpr (sizeof(S) != 2) {
             return (CT)0;
         } else {
-            const int k = reflected ? c0 : R::idx(cx + G::c(i, 0), cy + G::c(i, 1), cz + G::c(i, 2));
-            CT ud[3] = {0, 0, 0};
+            const int k = reflected ? c0 : R::template nb<HR::ZH>(G::c(i, 0), G::c(i, 1), G::c(i, 2));
+            CT f[F::NF], ud[3] = {0, 0, 0};
+            sC.get(kd, k, f);
 #pragma unroll
             for (int a = 0; a < DIMV; ++a)
-                if (G::c(i, a) != 0) ud[a] = sU[a][k];
+                if (G::c(i, a) != 0) ud[a] = f[F::U + a];
             CT cu = c_dot<G, DIMV>(i, ud);
             if (reflected) cu = -cu;
             return g_shift((CT)G::w(i), cu);
@@ -1540,8 +1677,10 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typena
         if constexpr (sizeof(S) != 2) {
             return (CT)0;
         } else {
-            const int k = reflected ? c0 : R::idx(cx + H::c(i, 0), cy + H::c(i, 1), cz + H::c(i, 2));
-            return (CT)H::w(i) * sPhi[k];
+            const int k = reflected ? c0 : R::template nb<HR::ZH>(H::c(i, 0), H::c(i, 1), H::c(i, 2));
+            CT f[F::NF];
+            sC.get(kd, k, f);
+            return (CT)H::w(i) * f[F::PHI];
         }
     };
     // rest direction of g, the opposite pairs, then the rest direction of h;
@@ -1563,11 +1702,9 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typena
     CT hmoved = 0;
 #pragma unroll
     for (int i = 1; i < G::Q; i += 2) {
-        // BF16 storage: keep the scheduler from interleaving pairs (its
-        // codec's integer rounding, hoisted across pairs, pushes the D3Q27
-        // kernel past its register budget into scratch spills; FP16 storage
-        // runs faster without the barrier)
-        if constexpr (std::is_same_v<S, uint16_t>) __builtin_amdgcn_sched_barrier(0);
+        // keep the scheduler from interleaving pairs (4-byte storage: more than
+        // two of them): the fewer registers buy another wave per SIMD
+        if (sizeof(S) != 4 || i / 2 % 2 == 0) __builtin_amdgcn_sched_barrier(0);
         const bool bi = WALL && nav_solid<G>(nv, i, +1);
         const bool bk = WALL && nav_solid<G>(nv, i + 1, +1);
         CT gi, gk;
@@ -1608,8 +1745,8 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typena
         aa_store<G, WALL, nts>(gs, nb, nv, i + 1, odd,
                                                          Codec<S>::enc(gk, gsc, gref_out(i + 1, bk)), bk);
         if (i < H::Q) {
-            const CT hi = Codec<S>::dec(sH[i][threadIdx.x], hisc, php * (CT)H::w(i));
-            const CT hk = Codec<S>::dec(sH[i + 1][threadIdx.x], hisc, php * (CT)H::w(i + 1));
+            const CT hi = Codec<S>::dec(h_in(i), hisc, php * (CT)H::w(i));
+            const CT hk = Codec<S>::dec(h_in(i + 1), hisc, php * (CT)H::w(i + 1));
             CT oi, ok;
             h_pair<H, DIMV, false>(ph, v, kc, i, hi, hk, &oi, &ok);
             const CT ri = href_out(i, bi), rk = href_out(i + 1, bk);
@@ -1625,17 +1762,28 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, typena
     // values sum to 1 + 1.5e-8 on D3Q19) and the rounding of identical bulk
     // nodes from drifting phi's mass step after step.
     {
-        const CT h0 = Codec<S>::dec(sH[0][threadIdx.x], hisc, php * (CT)H::w(0));
+        const CT h0 = Codec<S>::dec(h_in(0), hisc, php * (CT)H::w(0));
         aa_store<H, WALL, nts>(hs, nb, nv, 0, odd,
                                                          Codec<S>::enc(h0 + hmoved, hsc, href_out(0, true)), false);
     }
 }
 
-// Occupancy target of the collision kernel: 3 waves per SIMD.  Left alone
-// the compiler takes ~175-195 VGPRs (2 waves); a budget of 168 (3 waves)
-// costs a few dwords of spill and hides enough more memory latency to run
-// 10% (FP32) to 18% (FP16) faster; 128 (4 waves) spills too much.
-#define PULBM_COLLIDE_ATTR __attribute__((amdgpu_waves_per_eu(3, 3)))
+// Occupancy of the collision kernel: what bounds it in 2-byte storage is the
+// issue of vector instructions (about 1000 per wave) and the latency of its
+// loads, so it wants waves.  The least number of waves per SIMD is set here;
+// registers (tile_gradients) and LDS (h kept in registers, no u-rebuild halo
+// on lattice sets that never use it) allow 5 on even and 4 on odd steps in
+// 2-byte storage, 4 in 4-byte and 2 in 8-byte storage.  Against 3, 3 and 1
+// before (512x256x256 dam break, FP16, even / odd step: 1.46 / 1.75 -> 1.09 /
+// 1.47 ms; 101x53x45 FP64: 58 -> 45 us).  Held to 3 waves by LDS the FP16
+// collide takes 1.50 ms on average; asked for 5 waves on odd steps it spills
+// (1.57 ms).
+// (D3Q19 hydro in 4- and 8-byte storage: 3 and 1, by the LDS of the u rebuild.)
+template <int LS, class S> constexpr int collide_waves()
+{
+    return LS == 4 ? (sizeof(S) == 8 ? 1 : (sizeof(S) == 4 ? 3 : 4)) : (sizeof(S) == 8 ? 2 : 4);
+}
+#define PULBM_COLLIDE_ATTR __attribute__((amdgpu_waves_per_eu(collide_waves<LS, S>())))
 // One kernel per step parity: PAR 0 takes the tiles of cases at an even
 // step, with every load and store on its fixed slot (no branch: the FP16
 // collide's even steps run 17% faster than with the parity read at run
@@ -1653,21 +1801,21 @@ __global__ __launch_bounds__(256) PULBM_COLLIDE_ATTR void k_collide(CaseTab case
     using H = typename Mo::H;
     using CT = typename Codec<S>::CT;
     using R = typename Halo1<Mo, DIMV>::R;
-    __shared__ CT sPhi[R::N], sRho[R::N], sU[DIMV][R::N];
-    __shared__ S sH[H::Q][256];
-    // the new P two nodes deep, for cases whose collide rebuilds u (4- and 8-byte storage)
-    __shared__ CT sP2[sizeof(S) >= 4 ? Halo2<Mo, DIMV>::R::N : 1];
+    __shared__ TileCells<LS, S> sC;
+    __shared__ S sH[sizeof(S) == 2 ? 1 : H::Q][256];
+    // the new P two nodes deep, for cases whose collide rebuilds u
+    __shared__ CT sP2[can_fuse_u<LS, S>() ? Halo2<Mo, DIMV>::R::N : 1];
     const TileCtx t = tile_ctx<Mo>(cases, hdr, step_off);
     if (!t.active || (int)(t.step & 1) != PAR) return;
     CDesc& cs = *t.cs;
     if (tile_at_wall<Mo>(cs, t.ox, t.oy, t.oz)) {
-        collide_tile<LS, S, true, BGK, R, PAR>(cs, t, sPhi, sRho, sU, sH, sP2);
+        collide_tile<LS, S, true, BGK, R, PAR>(cs, t, sC, sH, sP2);
     } else if (PAR == 1 && t.ox >= 1 && t.ox + Mo::TX < cs.nx && t.oy >= 1 && t.oy + Mo::TY < cs.ny &&
                (DIMV == 2 || (t.oz >= 1 && t.oz + Mo::TZ < cs.nz))) {
         // every node of the tile has its neighbours inside the grid
-        collide_tile<LS, S, false, BGK, R, 2>(cs, t, sPhi, sRho, sU, sH, sP2);
+        collide_tile<LS, S, false, BGK, R, 2>(cs, t, sC, sH, sP2);
     } else {
-        collide_tile<LS, S, false, BGK, R, PAR>(cs, t, sPhi, sRho, sU, sH, sP2);
+        collide_tile<LS, S, false, BGK, R, PAR>(cs, t, sC, sH, sP2);
     }
 }
 
@@ -1685,7 +1833,8 @@ __global__ __launch_bounds__(256) void k_init(CaseTab cases, const int* hdr,
     using CT = typename Codec<S>::CT;
     using HR = Halo1<Mo, DIMV>;
     using R = typename HR::R;
-    __shared__ CT sPhi[R::N], sRho[R::N], sU[DIMV][R::N];
+    using F = CellF<DIMV>;
+    __shared__ TileCells<LS, S> sC;
     const TileCtx t = tile_ctx<Mo>(cases, hdr, 0);
     if (!t.active) return;
     CDesc& cs = *t.cs;
@@ -1699,14 +1848,15 @@ __global__ __launch_bounds__(256) void k_init(CaseTab cases, const int* hdr,
         if (k >= R::N) break;
         int off[3], cr;
         const uint32_t m = HR::cell(cs, t, k, off, &cr);
-        const CT f = (CT)phi0[m];
-        sPhi[k] = f;
-        sRho[k] = ph.rho_a + clamp01(f) * ph.drho;
+        CT f[F::NF];
+        f[F::PHI] = (CT)phi0[m];
+        f[F::RHO] = ph.rho_a + clamp01(f[F::PHI]) * ph.drho;
 #pragma unroll
         for (int a = 0; a < DIMV; ++a) {
             const CT ua = (CT)u0[(size_t)a * N + m];
-            sU[a][k] = (cr & 1) ? -ua : ua;
+            f[F::U + a] = (cr & 1) ? -ua : ua;
         }
+        sC.put(k, f);
     }
     __syncthreads();
     int lx, ly, lz;
@@ -1731,7 +1881,7 @@ __global__ __launch_bounds__(256) void k_init(CaseTab cases, const int* hdr,
         return;
     }
     NodeVals<CT> v;
-    tile_gradients<LS, R, CT>(sPhi, sRho, sU, lx + 1, ly + 1, lz + HR::ZH, v);
+    tile_gradients<LS, R, HR::ZH, grad_split_of<S, false, false, 0>()>(sC, sC.at(R::template nb_base<HR::ZH>(lx + 1, ly + 1, lz + HR::ZH)), v);
     const NodeCoef<DIMV, CT> kc = node_coef<DIMV, true, CT>(ph, v, (const CT*)nullptr);
     const CT hsc = cconst<CT>(cs.h_scale, cs.f32.h_scale), gsc = cconst<CT>(cs.g_scale, cs.f32.g_scale);
     // 2-byte storage: h_j - w_j phi0 (the previous-step phi of step 0 is phi0)

@@ -198,6 +198,7 @@ struct pulbm_case {
     CaseDev** tab = nullptr;  // device {d}
     int* hdr = nullptr;       // device tile table header {1, ntiles, 0, ntiles}
     int ntiles = 0;
+    int lds = 0;              // collide_lds
     int64_t step = 0;
     bool ready = false;
     int device = 0;           // device current at pulbm_create
@@ -209,7 +210,7 @@ namespace {
 
 template <int LS, class S>
 void launch_step(hipStream_t st, CaseDev* const* tab, const int* hdr, int blocks, int off, int which, bool bgk,
-                 int parity)
+                 int parity, int lds)
 {
     using CT = typename Codec<S>::CT;
     const dim3 grid(blocks), block(256);
@@ -219,25 +220,25 @@ void launch_step(hipStream_t st, CaseDev* const* tab, const int* hdr, int blocks
     if (which == 3) {
         // the collide kernel of each parity present (each skips the other's tiles)
         if (parity != 1) {
-            if (bgk) hipLaunchKernelGGL((k_collide<LS, S, true, 0>), grid, block, 0, st, tab, hdr, off);
-            else hipLaunchKernelGGL((k_collide<LS, S, false, 0>), grid, block, 0, st, tab, hdr, off);
+            if (bgk) hipLaunchKernelGGL((k_collide<LS, S, true, 0>), grid, block, lds, st, tab, hdr, off);
+            else hipLaunchKernelGGL((k_collide<LS, S, false, 0>), grid, block, lds, st, tab, hdr, off);
         }
         if (parity != 0) {
-            if (bgk) hipLaunchKernelGGL((k_collide<LS, S, true, 1>), grid, block, 0, st, tab, hdr, off);
-            else hipLaunchKernelGGL((k_collide<LS, S, false, 1>), grid, block, 0, st, tab, hdr, off);
+            if (bgk) hipLaunchKernelGGL((k_collide<LS, S, true, 1>), grid, block, lds, st, tab, hdr, off);
+            else hipLaunchKernelGGL((k_collide<LS, S, false, 1>), grid, block, lds, st, tab, hdr, off);
         }
     }
 }
 
 template <int LS>
 void launch_dim(int store, hipStream_t st, CaseDev* const* tab, const int* hdr, int blocks, int off, int which,
-                bool bgk, int parity)
+                bool bgk, int parity, int lds)
 {
     switch (store) {
-        case PULBM_STORE_FP64: launch_step<LS, double>(st, tab, hdr, blocks, off, which, bgk, parity); break;
-        case PULBM_STORE_FP32: launch_step<LS, float>(st, tab, hdr, blocks, off, which, bgk, parity); break;
-        case PULBM_STORE_FP16: launch_step<LS, _Float16>(st, tab, hdr, blocks, off, which, bgk, parity); break;
-        default: launch_step<LS, uint16_t>(st, tab, hdr, blocks, off, which, bgk, parity); break;
+        case PULBM_STORE_FP64: launch_step<LS, double>(st, tab, hdr, blocks, off, which, bgk, parity, lds); break;
+        case PULBM_STORE_FP32: launch_step<LS, float>(st, tab, hdr, blocks, off, which, bgk, parity, lds); break;
+        case PULBM_STORE_FP16: launch_step<LS, _Float16>(st, tab, hdr, blocks, off, which, bgk, parity, lds); break;
+        default: launch_step<LS, uint16_t>(st, tab, hdr, blocks, off, which, bgk, parity, lds); break;
     }
 }
 
@@ -246,13 +247,14 @@ void launch_dim(int store, hipStream_t st, CaseDev* const* tab, const int* hdr, 
 // parity: the step parity of every case of the table for this launch (its
 // device step counter plus off), 0 or 1, when the host knows it (a single
 // case); -1 when cases may differ (serving batches): then the collide
-// kernels of both parities are launched.
+// kernels of both parities are launched.  lds: LDS bytes the collide's
+// workgroups are given beyond their own (collide_lds).
 void launch(int ls, int store, bool bgk, hipStream_t st, CaseDev* const* tab, const int* hdr, int blocks, int off,
-            int which, int parity = -1)
+            int which, int parity = -1, int lds = 0)
 {
-    if (ls == 2) launch_dim<2>(store, st, tab, hdr, blocks, off, which, bgk, parity);
-    else if (ls == 4) launch_dim<4>(store, st, tab, hdr, blocks, off, which, bgk, parity);
-    else launch_dim<3>(store, st, tab, hdr, blocks, off, which, bgk, parity);
+    if (ls == 2) launch_dim<2>(store, st, tab, hdr, blocks, off, which, bgk, parity, lds);
+    else if (ls == 4) launch_dim<4>(store, st, tab, hdr, blocks, off, which, bgk, parity, lds);
+    else launch_dim<3>(store, st, tab, hdr, blocks, off, which, bgk, parity, lds);
 }
 
 template <int LS, class S>
@@ -274,6 +276,20 @@ void launch_init(int ls, int store, hipStream_t st, CaseDev* const* tab, const i
     }
     if (ls == 2) { PULBM_INIT_CASE(2) } else if (ls == 4) { PULBM_INIT_CASE(4) } else { PULBM_INIT_CASE(3) }
 #undef PULBM_INIT_CASE
+}
+
+// LDS bytes added to the collide's workgroups to hold them to 3 per CU instead
+// of 4.  4-byte D3Q27 populations past the 256 MB last-level cache are bound by
+// HBM, and a fourth workgroup only widens the set of halo rows that compete
+// for the L2 (measured with 3 / 4 per CU, step: 256^3 bubble 2.00 / 2.08 ms,
+// 128^3 droplet, 386 MB of populations, 244 / 249 us, 100^3 bubble 180 / 183
+// us); smaller grids are bound by latency and take 4 (90x75x70 BGK droplet
+// 102 / 94 us, 128x110x110 dam break 208 / 204 us).  D3Q19 hydro is held to 3
+// by the u rebuild's halo; the other storage widths gain from every workgroup.
+int collide_lds(const pulbm_params& p, int64_t nodes)
+{
+    const int64_t pops = (int64_t)(p.q_phase + p.q_hydro) * nodes * store_bytes(p.store);
+    return p.store == PULBM_STORE_FP32 && p.q_hydro == 27 && pops > (int64_t(320) << 20) ? 12 << 10 : 0;
 }
 
 // Codec constants.  FP16 stores h_j - w_j phi (phi of the reading node one
@@ -458,6 +474,7 @@ extern "C" int pulbm_create(const pulbm_params* p, void* dev_arena, size_t arena
                p->nx >= 3 && p->ny >= 3 && (p->dim == 2 || (p->nz >= 3 && p->q_hydro == 19));
     codec_constants(*p, h);
     derived_constants(h);
+    c->lds = collide_lds(*p, h.N);
     c->d = (CaseDev*)(c->base + L.desc);
     c->tab = (CaseDev**)(c->base + L.tab);
     c->hdr = (int*)(c->base + L.tab + sizeof(CaseDev*));
@@ -537,7 +554,7 @@ static void queue_direct(pulbm_case* c, int64_t first, int count)
         for (int w = 0; w < kStepKernels; ++w)
             if (w != kVelocityKernel || !c->h.fuse_u)
                 launch(lattice_set(c->p.dim, c->p.q_hydro), c->p.store, c->p.collision == 1, c->stream, c->tab,
-                       c->hdr, grid_of(c->ntiles), k, w, (int)((first + k) & 1));
+                       c->hdr, grid_of(c->ntiles), k, w, (int)((first + k) & 1), c->lds);
     hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, c->stream, c->tab, c->hdr, count);
 }
 
@@ -575,7 +592,7 @@ extern "C" int pulbm_step_timed(pulbm_case* c, int64_t nsteps, double* ms)
         for (int w = 0; w < kStepKernels; ++w) {
             if (w != kVelocityKernel || !c->h.fuse_u)
                 launch(lattice_set(c->p.dim, c->p.q_hydro), c->p.store, c->p.collision == 1, c->stream, c->tab,
-                       c->hdr, grid_of(c->ntiles), 0, w, (int)(c->step & 1));
+                       c->hdr, grid_of(c->ntiles), 0, w, (int)(c->step & 1), c->lds);
             (void)hipEventRecord(ev[w + 1], c->stream);
         }
         hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, c->stream, c->tab, c->hdr, 1);
