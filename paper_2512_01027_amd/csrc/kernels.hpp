@@ -49,11 +49,28 @@
 
 namespace pulbm {
 
+// The tiles of one shape that cover a case's grid, and their order.
+struct TileMap {
+    int32_t ntx, nty, ntz;  // tiles per axis
+    int32_t tband;          // tile rows per y band of the tile order (>= 1)
+    // The tile order's divisors -- ntx, tband ntz, tband and the last band's
+    // rows -- as multipliers M = floor(2^40 / d) + 1 split into high and low
+    // words, so that a block takes its tile apart with scalar multiplies:
+    // n / d = (n Mh + mulhi(n, Ml)) >> 8, exact while n d < 2^40 (fastdiv
+    // = 1, checked for every divisor against its largest dividend when the
+    // case is created; otherwise the kernels divide).
+    int32_t fastdiv;
+    uint32_t dvh[4], dvl[4];
+};
+
 // Per-case descriptor, resident in device memory (one per case of a launch).
 struct CaseDev {
     int32_t nx, ny, nz, dim;
     int32_t wall[3];
-    int32_t ntx, nty, ntz;  // tiles per axis
+    TileMap map;   // the lattice set's tiles (Model)
+    TileMap wide;  // the tiles of k_pressure_wide and k_velocity_wide (3D)
+    int32_t near_lo[3], near_n[3];  // the box of wide tiles whose halo reaches the block
+    int32_t near_subs;  // their tiles of the lattice set's shape, rounded up to 8 (0: no block)
     int32_t delta_theta;
     int32_t sx;        // row pitch in nodes: nx rounded up to 32, so that every row of a
                        // tile starts on a 128-byte line (node n = x + sx (y + ny z))
@@ -78,18 +95,9 @@ struct CaseDev {
     double p_top;           // pressure of an open high end (wall = 2 on the last axis)
     int32_t blk_lo[3], blk_hi[3];  // solid block, nodes lo <= x < hi (has_block)
     int32_t has_block;
-    int32_t tband;  // tile rows per y band of the tile order (>= 1)
     int32_t fuse_u; // 1: the collide kernel rebuilds u itself and a step skips k_velocity
                     // (no wall, open end or block, 4- or 8-byte storage, every axis >= 3,
                     // D2Q9 or D3Q19 hydro)
-    // The tile order's divisors -- ntx, tband ntz, tband and the last band's
-    // rows -- as multipliers M = floor(2^40 / d) + 1 split into high and low
-    // words, so that a block takes its tile apart with scalar multiplies:
-    // n / d = (n Mh + mulhi(n, Ml)) >> 8, exact while n d < 2^40 (fastdiv
-    // = 1, checked for every divisor against its largest dividend when the
-    // case is created; otherwise the kernels divide).
-    int32_t fastdiv;
-    uint32_t dvh[4], dvl[4];
     int32_t tile_rev;  // 1: the case's tiles are taken in reverse order (a race check, pulbm_set_tile_order)
     int32_t nt_odd_moments;  // 1: k_moments streams its 4- and 8-byte loads on odd steps too
     // Constants of the collision derived once on the host (so no thread
@@ -124,7 +132,7 @@ __device__ __forceinline__ int xcd_tile(int bid, int nblocks)
     return (bid & 7) * per + (bid >> 3);
 }
 
-// n / d for the multiplier (mh, ml) of d (CaseDev::dvh, dvl): the high word
+// n / d for the multiplier (mh, ml) of d (TileMap::dvh, dvl): the high word
 // of n times the 40-bit multiplier, shifted down by 8.  n mh stays below 2^32
 // for n < 2^23 (mh <= 256).
 __device__ __forceinline__ uint32_t udiv_m(uint32_t n, uint32_t mh, uint32_t ml)
@@ -150,6 +158,34 @@ struct TileCtx {
     bool active;
 };
 
+// Tile lt of a case, in the tile order: x fastest, then z within a band of
+// tband tile rows, then the bands along y.  Tiles that share z-halo rows then
+// run close together (a band's width of tiles apart), while each plane is
+// still read in runs of whole rows.
+__device__ __forceinline__ void tile_xyz(const PULBM_CST TileMap& m, int lt, int* tx, int* ty, int* tz)
+{
+    if (m.fastdiv) {
+        const uint32_t l = (uint32_t)lt;
+        const uint32_t r = udiv_m(l, m.dvh[0], m.dvl[0]);
+        *tx = (int)(l - r * (uint32_t)m.ntx);
+        const uint32_t yb = udiv_m(r, m.dvh[1], m.dvl[1]);
+        const uint32_t rem = r - yb * (uint32_t)(m.tband * m.ntz);
+        const int rows = m.nty - (int)yb * m.tband;  // rows of this band: tband, or fewer in the last
+        const int k = rows < m.tband ? 3 : 2;
+        const uint32_t tq = udiv_m(rem, m.dvh[k], m.dvl[k]);
+        *tz = (int)tq;
+        *ty = (int)yb * m.tband + (int)(rem - tq * (uint32_t)min(m.tband, rows));
+    } else {
+        *tx = lt % m.ntx;
+        lt /= m.ntx;
+        const int yb = lt / (m.tband * m.ntz);
+        const int rem = lt - yb * m.tband * m.ntz;
+        const int by = min(m.tband, m.nty - yb * m.tband);
+        *tz = rem / by;
+        *ty = yb * m.tband + rem % by;
+    }
+}
+
 template <class Mo>
 __device__ __forceinline__ TileCtx tile_ctx(CaseTab cases, const int* hdr_, int step_off)
 {
@@ -173,36 +209,57 @@ __device__ __forceinline__ TileCtx tile_ctx(CaseTab cases, const int* hdr_, int 
     // whatever the case's step limit)
     t.step = cs.step + (step_off > 0 ? step_off : 0);
     t.active = step_off < 0 || t.step < cs.step_end;
-    // tile order: x fastest, then z within a band of tband tile rows, then
-    // the bands along y.  Tiles that share z-halo rows then run close together
-    // (a band's width of tiles apart), while each plane is still read in runs
-    // of whole rows.
     int lt = tile - tstart[ci];
     if (cs.tile_rev) lt = tstart[ci + 1] - tstart[ci] - 1 - lt;
     int tx, ty, tz;
-    if (cs.fastdiv) {
-        const uint32_t l = (uint32_t)lt;
-        const uint32_t r = udiv_m(l, cs.dvh[0], cs.dvl[0]);
-        tx = (int)(l - r * (uint32_t)cs.ntx);
-        const uint32_t yb = udiv_m(r, cs.dvh[1], cs.dvl[1]);
-        const uint32_t rem = r - yb * (uint32_t)(cs.tband * cs.ntz);
-        const int rows = cs.nty - (int)yb * cs.tband;  // rows of this band: tband, or fewer in the last
-        const int k = rows < cs.tband ? 3 : 2;
-        const uint32_t tq = udiv_m(rem, cs.dvh[k], cs.dvl[k]);
-        tz = (int)tq;
-        ty = (int)yb * cs.tband + (int)(rem - tq * (uint32_t)min(cs.tband, rows));
-    } else {
-        tx = lt % cs.ntx;
-        lt /= cs.ntx;
-        const int yb = lt / (cs.tband * cs.ntz);
-        const int rem = lt - yb * cs.tband * cs.ntz;
-        const int by = min(cs.tband, cs.nty - yb * cs.tband);
-        tz = rem / by;
-        ty = yb * cs.tband + rem % by;
-    }
+    tile_xyz(cs.map, lt, &tx, &ty, &tz);
     t.ox = tx * Mo::TX;
     t.oy = ty * Mo::TY;
     t.oz = tz * Mo::TZ;
+    return t;
+}
+
+// Tile shape of k_pressure_wide and k_velocity_wide: four nodes to a thread,
+// one above the other in z.
+struct WideTile {
+    static constexpr int TX = 64, TY = 4, TZ = 4;
+};
+
+// The wide tile of a block of a single case's launch (the table's only case).
+// Wide tiles near the solid block, whose ghosts mirror cell by cell, are taken
+// as tiles of the lattice set's shape, a block each (*sub; the first near_subs
+// blocks): one after another in the wide tile's own block they held up the XCD
+// whose run holds them (293 x 91 x 91 with a block: pressure 41 us).
+template <class Mo> __device__ __forceinline__ TileCtx wide_ctx(CaseTab cases, int step_off, bool* sub)
+{
+    TileCtx t;
+    t.cs = (CDesc*)(uintptr_t)*(const PULBM_CST uint64_t*)(const void*)cases;
+    CDesc& cs = *t.cs;
+    t.step = cs.step + (step_off > 0 ? step_off : 0);
+    *sub = (int)blockIdx.x < cs.near_subs;
+    if (*sub) {
+        constexpr int SY = WideTile::TY / Mo::TY, SUBS = SY * (WideTile::TZ / Mo::TZ);
+        const int k = (int)blockIdx.x % SUBS, w = (int)blockIdx.x / SUBS;
+        const int wx = w % cs.near_n[0], wy = w / cs.near_n[0] % cs.near_n[1], wz = w / (cs.near_n[0] * cs.near_n[1]);
+        t.ox = (cs.near_lo[0] + wx) * WideTile::TX;
+        t.oy = (cs.near_lo[1] + wy) * WideTile::TY + k % SY * Mo::TY;
+        t.oz = (cs.near_lo[2] + wz) * WideTile::TZ + k / SY * Mo::TZ;
+        t.active = wz < cs.near_n[2] && t.oy < cs.ny && t.oz < cs.nz && (step_off < 0 || t.step < cs.step_end);
+        return t;
+    }
+    const int bid = (int)blockIdx.x - cs.near_subs;
+    const int total = cs.wide.ntx * cs.wide.nty * cs.wide.ntz, used = (total + 7) & ~7;
+    t.active = bid < used;
+    if (!t.active) return t;
+    int lt = xcd_tile(bid, used);
+    t.active = lt < total && (step_off < 0 || t.step < cs.step_end);
+    if (!t.active) return t;
+    if (cs.tile_rev) lt = total - 1 - lt;
+    int tx, ty, tz;
+    tile_xyz(cs.wide, lt, &tx, &ty, &tz);
+    t.ox = tx * WideTile::TX;
+    t.oy = ty * WideTile::TY;
+    t.oz = tz * WideTile::TZ;
     return t;
 }
 
@@ -535,6 +592,8 @@ struct Halo1 {
     static constexpr int ZH = DIMV == 3 ? 1 : 0;
     static constexpr int RX = Mo::TX + 2, RY = Mo::TY + 2, RZ = Mo::TZ + 2 * ZH;
     using R = Region<RX, RY, RZ>;
+    static constexpr bool VEC = false;  // LDS cells are written one by one
+    __device__ static __forceinline__ int slot(int k) { return k; }
     // BND: the tile touches a wall, the open end or the block (tiles that do
     // not never meet the block, and skip its test)
     template <bool BND = true>
@@ -575,6 +634,8 @@ struct Halo2 {
     static constexpr int ZH = DIMV == 3 ? 2 : 0;
     static constexpr int RX = Mo::TX + 4, RY = Mo::TY + 4, RZ = Mo::TZ + 2 * ZH;
     using R = Region<RX, RY, RZ>;
+    static constexpr bool VEC = false;
+    __device__ static __forceinline__ int slot(int k) { return k; }
     template <bool BND = false>
     __device__ static __forceinline__ uint32_t cell(CDesc& cs, const TileCtx& t, int k, int off[3], int* cr)
     {
@@ -585,6 +646,23 @@ struct Halo2 {
         const int y = resolve_axis(t.oy - 2 + iy, cs.ny, 0, &off[1], cr);
         const int z = resolve_axis(t.oz - ZH + iz, cs.nz, 0, &off[2], cr);
         return (uint32_t)x + (uint32_t)cs.sx * ((uint32_t)y + (uint32_t)cs.ny * (uint32_t)z);
+    }
+};
+
+// The 1-halo region of a wide tile.  Its rows start at cell 3 of a pitch of 68
+// in LDS (the last of a row's 66 cells takes the next row's unused first), so
+// that a row's interior starts on 16 bytes (in 4-byte fields) and is written as
+// the 4-element vectors it is read in.
+struct HaloW : Halo1<WideTile, 3> {
+    using B = Halo1<WideTile, 3>;
+    struct R {
+        static constexpr int PITCH = 68, N = PITCH * B::RY * B::RZ + 4;
+        __device__ static __forceinline__ int idx(int ix, int iy, int iz) { return 3 + ix + PITCH * (iy + B::RY * iz); }
+    };
+    static constexpr bool VEC = true;
+    __device__ static __forceinline__ int slot(int k)
+    {
+        return R::idx(k % B::RX, (k / B::RX) % B::RY, k / (B::RX * B::RY));
     }
 };
 
@@ -676,7 +754,11 @@ __device__ __forceinline__ void halo_rows(CDesc& cs, const TileCtx& t, void* con
     }
     if constexpr (FENCE) __builtin_amdgcn_sched_barrier(0);  // every load issued, then the LDS writes
 #pragma unroll
-    for (int p = 0; p < PV; ++p)
+    for (int p = 0; p < PV; ++p) {
+        if constexpr (HR::VEC) {
+            store(kv[p], crv[p], offv[p], v[p]);
+            continue;
+        }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             CT w[NV];
@@ -684,6 +766,7 @@ __device__ __forceinline__ void halo_rows(CDesc& cs, const TileCtx& t, void* con
             for (int j = 0; j < NV; ++j) w[j] = v[p][j][c];
             store(kv[p] + c, crv[p], offv[p], w);
         }
+    }
 #pragma unroll
     for (int p = 0; p < PE; ++p) store(ke[p], cre[p], offe[p], e[p]);
 }
@@ -712,19 +795,24 @@ __device__ __forceinline__ void halo_stage(CDesc& cs, const TileCtx& t, void* co
             }
         }
     }
-    constexpr int RN = HR::R::N;
-    constexpr int NIT = (RN + 255) / 256;
-    CT v[NIT][NV];
-    int cr[NIT], off[NIT][3];
+    constexpr int RN = HR::RX * HR::RY * HR::RZ;
+    // all loads of up to 5 cells a thread before their LDS writes
+    constexpr int NIT = (RN + 255) / 256, STEP = NIT < 5 ? NIT : 5;
+#pragma unroll 1
+    for (int i0 = 0; i0 < NIT; i0 += STEP) {
+        CT v[STEP][NV];
+        int cr[STEP], off[STEP][3];
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int k = min((int)threadIdx.x + 256 * it, RN - 1);
-        const uint32_t m = HR::template cell<WALL>(cs, t, k, off[it], &cr[it]);
+        for (int it = 0; it < STEP; ++it) {
+            const int k = min((int)threadIdx.x + 256 * (i0 + it), RN - 1);
+            const uint32_t m = HR::template cell<WALL>(cs, t, k, off[it], &cr[it]);
 #pragma unroll
-        for (int j = 0; j < NV; ++j) v[it][j] = *at_node<CT>(src[j], m);
+            for (int j = 0; j < NV; ++j) v[it][j] = *at_node<CT>(src[j], m);
+        }
+#pragma unroll
+        for (int it = 0; it < STEP; ++it)
+            store(HR::slot(min((int)threadIdx.x + 256 * (i0 + it), RN - 1)), cr[it], off[it], v[it]);
     }
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) store(min((int)threadIdx.x + 256 * it, RN - 1), cr[it], off[it], v[it]);
 }
 
 // ------------------------------------------------------------ physics
@@ -1359,6 +1447,270 @@ __global__ __launch_bounds__(256) void k_velocity(CaseTab cases, const int* hdr,
     if (cs.fuse_u && step_off >= 0) return;
     if (tile_at_wall<Mo>(cs, t.ox, t.oy, t.oz)) velocity_tile<LS, CT, true, R>(cs, t, sP, sGD);
     else velocity_tile<LS, CT, false, R>(cs, t, sP, sGD);
+}
+
+// --- pressure and velocity of large 3D cases in 4-byte fields: wide tiles, four
+// nodes to a thread, one above the other in z (64 x 4 x 4 nodes).  k_pressure
+// and k_velocity are bound by the issue of vector instructions (280 and 171 per
+// wave and node, half of it addressing and halo work).  Here the halo is 2.3
+// cells a node instead of 4.1, its rows go to LDS as vectors, and a thread
+// slides a 3x3x3 window up its column, which reads 13.5 cells a node from LDS
+// instead of 27 (186 and 104 instructions).  The arithmetic of a node is
+// k_pressure's and k_velocity's, term by term.  512x256x256 dam break:
+// pressure 313 -> 238 us (3.4 TB/s; its FP64 sums and 12 LDS words a cell keep
+// it from the copy's 6.3), velocity 227 -> 185 us (5.8 TB/s).  LDS and registers
+// hold 4 (pressure) and 5 (velocity) workgroups per CU; pressure at 3: 264 us.
+
+// f of a value, or of each element of a vector of them.
+template <class T, class F> __device__ __forceinline__ T each(T v, F f)
+{
+    if constexpr (std::is_arithmetic_v<T>) {
+        return f(v);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = f(v[c]);
+        return v;
+    }
+}
+template <class T, class CT> __device__ __forceinline__ void lds_put(CT* s, int k, T v) { *(T*)(s + k) = v; }
+
+// Three planes of 3x3 cells of an LDS field around a column of a wide tile,
+// plane p of the column (its first node at p = 1) in slot p % 3.  The planes are
+// read in order through one LDS address, hidden from the compiler: it would
+// read them all at once (200 registers), and pair reads through addresses of
+// their own.
+template <class CT> struct Window {
+    const __attribute__((address_space(3))) CT* next;
+    CT v[3][9];
+    __device__ __forceinline__ void start(const CT* s, int lx, int ly)
+    {
+        next = (const __attribute__((address_space(3))) CT*)(s + HaloW::R::idx(lx, ly, 0));
+    }
+    __device__ __forceinline__ void load(int p)
+    {
+        asm volatile("" : "+v"(next));
+#pragma unroll
+        for (int n = 0; n < 9; ++n) v[p % 3][n] = next[n % 3 + HaloW::R::PITCH * (n / 3)];
+        next += HaloW::R::PITCH * HaloW::RY;
+    }
+    // the cell at (dx, dy, dz) from node q of the column
+    __device__ __forceinline__ CT at(int q, int dx, int dy, int dz) const
+    {
+        return v[(q + 1 + dz) % 3][1 + dx + 3 * (1 + dy)];
+    }
+};
+
+// The hydrostatic part of P at the cells around a column's nodes, in a tile at
+// a wall and clear of the block: g . (ghost - mirror), 0 inside the grid and
+// beyond an open end.  Formed where it is used: kept in LDS it would cost the
+// fourth workgroup per CU, kept in registers the fourth wave.
+template <class CT> struct Ghosts {
+    double gx[2], gy[2], gz[2];
+    bool open;
+    __device__ __forceinline__ void column(CDesc& cs, int x, int y)
+    {
+        gx[0] = cs.wall[0] && x == 0 ? -cs.grav[0] : 0.0;
+        gx[1] = cs.wall[0] && x == cs.nx - 1 ? cs.grav[0] : 0.0;
+        gy[0] = cs.wall[1] && y == 0 ? -cs.grav[1] : 0.0;
+        gy[1] = cs.wall[1] && y == cs.ny - 1 ? cs.grav[1] : 0.0;
+    }
+    __device__ __forceinline__ void node(CDesc& cs, int z)
+    {
+        gz[0] = cs.wall[2] && z == 0 ? -cs.grav[2] : 0.0;
+        gz[1] = cs.wall[2] && z == cs.nz - 1 ? cs.grav[2] : 0.0;
+        open = cs.wall[2] == 2 && z == cs.nz - 1;
+    }
+    __device__ __forceinline__ CT at(int dx, int dy, int dz) const
+    {
+        double g = dx < 0 ? gx[0] : (dx > 0 ? gx[1] : 0.0);
+        if (dy != 0) g = g + (dy < 0 ? gy[0] : gy[1]);
+        if (dz != 0) g = g + (dz < 0 ? gz[0] : gz[1]);
+        return dz > 0 && open ? (CT)0 : (CT)g;
+    }
+};
+
+template <int LS, class AT, bool WALL>
+__device__ __forceinline__ void pressure_wide(CDesc& cs, const TileCtx& t, AT* sP, AT (*sJ)[HaloW::R::N])
+{
+    using G = typename Model<LS>::G;
+    using W = WideTile;
+    const Slots<AT> Js = slots<AT>(cs.J, cs.N);
+    const int lx = threadIdx.x % W::TX, ly = threadIdx.x / W::TX;
+    const int x = t.ox + lx, y = t.oy + ly;
+    const uint32_t n0 = (uint32_t)x + (uint32_t)cs.sx * ((uint32_t)y + (uint32_t)cs.ny * (uint32_t)t.oz);
+    const uint32_t pl = (uint32_t)cs.sx * (uint32_t)cs.ny;
+    const bool col = x < cs.nx && y < cs.ny;
+    // the nodes' own phi is loaded first, so its latency overlaps the halo's
+    AT phi[W::TZ];
+#pragma unroll
+    for (int q = 0; q < W::TZ; ++q)
+        phi[q] = col && t.oz + q < cs.nz ? __builtin_nontemporal_load(at_node<AT>(cs.phi[t.step & 1], n0 + q * pl)) : (AT)0;
+    void* src[4] = {cs.Ps, (void*)Js.at(0, 0), (void*)Js.at(1, 0), (void*)Js.at(2, 0)};
+    halo_stage<HaloW, WALL, 4, AT>(cs, t, src, [&](int k, int cr, const int*, const auto* v) {
+        auto p = v[0];
+        if (WALL && (cr & kOpenGhost)) p = each(p, [&](AT q) { return (AT)(2.0 * cs.p_top - (double)q); });
+        lds_put(sP, k, p);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            auto j = v[1 + a];
+            if (WALL && (cr & 1)) j = each(j, [&](AT q) { return (AT)(-(double)q + 2.0 * cs.grav[a]); });
+            lds_put(sJ[a], k, j);
+        }
+    });
+    __syncthreads();
+    if (!col) return;
+    Window<AT> wP, wJ[3];
+    Ghosts<AT> gd;
+    wP.start(sP, lx, ly);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) wJ[a].start(sJ[a], lx, ly);
+    if (WALL) gd.column(cs, x, y);
+    auto plane = [&](int p) {
+        wP.load(p);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) wJ[a].load(p);
+    };
+    plane(0);
+    plane(1);
+    constexpr int NS = shell<G>(G::Q - 1) + 1;
+#pragma unroll
+    for (int q = 0; q < W::TZ; ++q) {
+        plane(q + 2);
+        const int z = t.oz + q;
+        if (WALL) gd.node(cs, z);
+        const double drho = (double)clamp01(phi[q]) * (cs.rho_w - cs.rho_a);
+        const double rho = cs.rho_a + drho;
+        const AT P0 = wP.at(q, 0, 0, 0);
+        AT sks[NS], sgs[NS], dus[3][NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) sks[s] = sgs[s] = dus[0][s] = dus[1][s] = dus[2][s] = 0;
+#pragma unroll
+        for (int i = 1; i < G::Q; i += 2) {  // pairs (i, i+1) are opposite
+            const int s = shell<G>(i), cx = G::c(i, 0), cy = G::c(i, 1), cz = G::c(i, 2);
+            sks[s] += (wP.at(q, -cx, -cy, -cz) - P0) + (wP.at(q, cx, cy, cz) - P0);
+            if (WALL) sgs[s] += gd.at(-cx, -cy, -cz) + gd.at(cx, cy, cz);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                if (G::c(i, a) == 0) continue;
+                const AT d = wJ[a].at(q, -cx, -cy, -cz) - wJ[a].at(q, cx, cy, cz);
+                if (G::c(i, a) == 1) dus[a][s] += d;
+                else dus[a][s] -= d;
+            }
+        }
+        double sk = 0, sg = 0, su = 0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const double w = shell_w<G>(s);
+            sk += w * (double)sks[s];
+            if (WALL) sg += w * (double)sgs[s];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) su += w * (double)dus[a][s];
+        }
+        if (WALL) sk += rho * sg;
+        AT P = (AT)((double)P0 + (sk + drho * su));
+        asm volatile("" : "+v"(P));
+        if (z < cs.nz) *at_node<AT>(cs.P[(t.step + 1) & 1], n0 + q * pl) = P;
+    }
+}
+
+template <int LS, class AT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_pressure_wide(CaseTab cases, int step_off)
+{
+    using R = HaloW::R;
+    using S = typename Halo1<Model<LS>, 3>::R;
+    __shared__ __align__(16) AT sP[R::N], sJ[3][R::N];
+    static_assert(2 * S::N <= R::N, "a sub-tile's fields fit");
+    bool sub;
+    const TileCtx t = wide_ctx<Model<LS>>(cases, step_off, &sub);
+    if (!t.active) return;
+    CDesc& cs = *t.cs;
+    if (sub) pressure_tile<LS, AT, true, S>(cs, t, sP, sP + S::N, (AT(*)[S::N])sJ);
+    else if (halo_near_block<HaloW>(cs, t)) return;
+    else if (tile_at_wall<WideTile>(cs, t.ox, t.oy, t.oz)) pressure_wide<LS, AT, true>(cs, t, sP, sJ);
+    else pressure_wide<LS, AT, false>(cs, t, sP, sJ);
+}
+
+template <int LS, class CT, bool WALL>
+__device__ __forceinline__ void velocity_wide(CDesc& cs, const TileCtx& t, CT* sP)
+{
+    using G = typename Model<LS>::G;
+    using W = WideTile;
+    const Slots<CT> Js = slots<CT>(cs.J, cs.N), Us = slots<CT>(cs.U[t.step & 1], cs.N);
+    const int lx = threadIdx.x % W::TX, ly = threadIdx.x / W::TX;
+    const int x = t.ox + lx, y = t.oy + ly;
+    const uint32_t n0 = (uint32_t)x + (uint32_t)cs.sx * ((uint32_t)y + (uint32_t)cs.ny * (uint32_t)t.oz);
+    const uint32_t pl = (uint32_t)cs.sx * (uint32_t)cs.ny;
+    const bool col = x < cs.nx && y < cs.ny;
+    // the nodes' own operands are loaded first, so their latency overlaps the halo's
+    CT phi[W::TZ], J[W::TZ][3];
+#pragma unroll
+    for (int q = 0; q < W::TZ; ++q) {
+        phi[q] = J[q][0] = J[q][1] = J[q][2] = 0;
+        if (col && t.oz + q < cs.nz) {
+            phi[q] = __builtin_nontemporal_load(at_node<CT>(cs.phi[t.step & 1], n0 + q * pl));
+#pragma unroll
+            for (int a = 0; a < 3; ++a) J[q][a] = __builtin_nontemporal_load(Js.at(a, (n0 + q * pl) * (uint32_t)sizeof(CT)));
+        }
+    }
+    void* src[1] = {cs.P[(t.step + 1) & 1]};
+    halo_stage<HaloW, WALL, 1, CT>(cs, t, src, [&](int k, int cr, const int*, const auto* v) {
+        auto p = v[0];
+        if (WALL && (cr & kOpenGhost)) p = each(p, [&](CT q) { return (CT)(2.0 * cs.p_top - (double)q); });
+        lds_put(sP, k, p);
+    });
+    __syncthreads();
+    if (!col) return;
+    const CT ra = cconst<CT>(cs.rho_a, cs.f32.rho_a), dr = cconst<CT>(cs.rho_w - cs.rho_a, cs.f32.drho);
+    Window<CT> wP;
+    Ghosts<CT> gd;
+    wP.start(sP, lx, ly);
+    if (WALL) gd.column(cs, x, y);
+    wP.load(0);
+    wP.load(1);
+#pragma unroll
+    for (int q = 0; q < W::TZ; ++q) {
+        wP.load(q + 2);
+        const int z = t.oz + q;
+        if (WALL) gd.node(cs, z);
+        const uint32_t na = (n0 + q * pl) * (uint32_t)sizeof(CT);
+        const CT rho = ra + clamp01(phi[q]) * dr;
+        const CT irho = rcp(rho);
+        CT gr[3] = {0, 0, 0};
+#pragma unroll
+        for (int i = 1; i < G::Q; i += 2) {
+            const int cx = G::c(i, 0), cy = G::c(i, 1), cz = G::c(i, 2);
+            const CT p = wP.at(q, cx, cy, cz), m = wP.at(q, -cx, -cy, -cz);
+            const CT d = (WALL ? (p + rho * gd.at(cx, cy, cz)) - (m + rho * gd.at(-cx, -cy, -cz)) : p - m) * (CT)G::w(i);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                if (G::c(i, a) == 1) gr[a] += d;
+                if (G::c(i, a) == -1) gr[a] -= d;
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) asm volatile("" : "+v"(gr[a]));
+        if (z < cs.nz) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) *Us.at(a, na) = J[q][a] - gr[a] * (CT)3.0 * irho;
+        }
+    }
+}
+
+template <int LS, class CT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_velocity_wide(CaseTab cases, int step_off)
+{
+    using R = HaloW::R;
+    using S = typename Halo1<Model<LS>, 3>::R;
+    __shared__ __align__(16) CT sP[R::N];
+    bool sub;
+    const TileCtx t = wide_ctx<Model<LS>>(cases, step_off, &sub);
+    if (!t.active) return;
+    CDesc& cs = *t.cs;
+    if (cs.fuse_u && step_off >= 0) return;
+    if (sub) velocity_tile<LS, CT, true, S>(cs, t, sP, sP + S::N);
+    else if (halo_near_block<HaloW>(cs, t)) return;
+    else if (tile_at_wall<WideTile>(cs, t.ox, t.oy, t.oz)) velocity_wide<LS, CT, true>(cs, t, sP);
+    else velocity_wide<LS, CT, false>(cs, t, sP);
 }
 
 // Fields of a cell of the collide and init tiles, in LDS order: phi, u, rho.

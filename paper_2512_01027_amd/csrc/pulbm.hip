@@ -152,31 +152,32 @@ int validate(const pulbm_params* p)
     return PULBM_OK;
 }
 
-// Multipliers of the tile order's divisors (CaseDev::dvh, dvl): M =
-// floor(2^40 / d) + 1 gives floor(n M / 2^40) = n / d for n d < 2^40, since
-// M d - 2^40 lies in [1, d].  fastdiv is set when that holds for every
-// divisor and its largest dividend, and the tile count is below 2^23.
-void tile_divisors(CaseDev& h, int64_t ntiles)
+// The tiles of one shape over the grid, and the multipliers of the tile
+// order's divisors (TileMap::dvh, dvl): M = floor(2^40 / d) + 1 gives
+// floor(n M / 2^40) = n / d for n d < 2^40, since M d - 2^40 lies in [1, d].
+// fastdiv is set when that holds for every divisor and its largest dividend,
+// and the tile count is below 2^23.
+template <class Tile> TileMap tile_map(const pulbm_params& p, int tband)
 {
-    const int64_t nb = (h.nty + h.tband - 1) / h.tband;
-    const int64_t d[4] = {h.ntx, (int64_t)h.tband * h.ntz, h.tband, h.nty - (nb - 1) * h.tband};
-    const int64_t nmax[4] = {ntiles, ntiles / h.ntx + 1, (int64_t)h.tband * h.ntz, (int64_t)h.tband * h.ntz};
+    TileMap m;
+    std::memset(&m, 0, sizeof m);
+    m.ntx = (p.nx + Tile::TX - 1) / Tile::TX;
+    m.nty = (p.ny + Tile::TY - 1) / Tile::TY;
+    m.ntz = (p.nz + Tile::TZ - 1) / Tile::TZ;
+    m.tband = tband;
+    const int64_t ntiles = (int64_t)m.ntx * m.nty * m.ntz;
+    const int64_t nb = (m.nty + m.tband - 1) / m.tband;
+    const int64_t d[4] = {m.ntx, (int64_t)m.tband * m.ntz, m.tband, m.nty - (nb - 1) * m.tband};
+    const int64_t nmax[4] = {ntiles, ntiles / m.ntx + 1, (int64_t)m.tband * m.ntz, (int64_t)m.tband * m.ntz};
     bool ok = ntiles < (int64_t(1) << 23);
     for (int k = 0; k < 4; ++k) {
-        const uint64_t m = (uint64_t(1) << 40) / (uint64_t)d[k] + 1;
-        h.dvh[k] = (uint32_t)(m >> 32);
-        h.dvl[k] = (uint32_t)m;
+        const uint64_t q = (uint64_t(1) << 40) / (uint64_t)d[k] + 1;
+        m.dvh[k] = (uint32_t)(q >> 32);
+        m.dvl[k] = (uint32_t)q;
         ok = ok && d[k] >= 1 && (uint64_t)nmax[k] * (uint64_t)d[k] < (uint64_t(1) << 40);
     }
-    h.fastdiv = ok ? 1 : 0;
-}
-
-template <int LS> void tiles_of(const pulbm_params& p, int* ntx, int* nty, int* ntz)
-{
-    using Mo = Model<LS>;
-    *ntx = (p.nx + Mo::TX - 1) / Mo::TX;
-    *nty = (p.ny + Mo::TY - 1) / Mo::TY;
-    *ntz = (p.nz + Mo::TZ - 1) / Mo::TZ;
+    m.fastdiv = ok ? 1 : 0;
+    return m;
 }
 
 int grid_of(int tiles) { return ((tiles + 7) / 8) * 8; }
@@ -198,6 +199,7 @@ struct pulbm_case {
     CaseDev** tab = nullptr;  // device {d}
     int* hdr = nullptr;       // device tile table header {1, ntiles, 0, ntiles}
     int ntiles = 0;
+    int nwide = 0;            // wide tiles, if pressure and velocity take them (0: they do not)
     int lds = 0;              // collide_lds
     int64_t step = 0;
     bool ready = false;
@@ -227,6 +229,20 @@ void launch_step(hipStream_t st, CaseDev* const* tab, const int* hdr, int blocks
             if (bgk) hipLaunchKernelGGL((k_collide<LS, S, true, 1>), grid, block, lds, st, tab, hdr, off);
             else hipLaunchKernelGGL((k_collide<LS, S, false, 1>), grid, block, lds, st, tab, hdr, off);
         }
+    }
+}
+
+// Pressure (which 1) or velocity (which 2) of a single large 3D case in 4-byte
+// fields, on wide tiles.
+void launch_wide(int ls, hipStream_t st, CaseDev* const* tab, int blocks, int off, int which)
+{
+    const dim3 grid(blocks), block(256);
+    if (which == 1) {
+        if (ls == 4) hipLaunchKernelGGL((k_pressure_wide<4, float>), grid, block, 0, st, tab, off);
+        else hipLaunchKernelGGL((k_pressure_wide<3, float>), grid, block, 0, st, tab, off);
+    } else {
+        if (ls == 4) hipLaunchKernelGGL((k_velocity_wide<4, float>), grid, block, 0, st, tab, off);
+        else hipLaunchKernelGGL((k_velocity_wide<3, float>), grid, block, 0, st, tab, off);
     }
 }
 
@@ -292,6 +308,36 @@ int collide_lds(const pulbm_params& p, int64_t nodes)
     return p.store == PULBM_STORE_FP32 && p.q_hydro == 27 && pops > (int64_t(320) << 20) ? 12 << 10 : 0;
 }
 
+// Do pressure and velocity take wide tiles?  With 4-byte fields in 3D, from
+// 2048 tiles (512 wide ones, two to a CU) up: measured, pressure + velocity,
+// narrow / wide tiles, 96^3 34.5 / 33.7 us, 128 x 64 x 64 23.9 / 21.9 us,
+// 128^3 45 / 40 us, 512 x 256 x 256 539 / 424 us, but 64^3 16.7 / 19.3 us: too
+// few workgroups, each four times as long.  8-byte fields would leave one
+// workgroup per CU.
+bool wide_tiles(const pulbm_params& p, int ntiles)
+{
+    return p.dim == 3 && aux_bytes(p.store) == 4 && ntiles >= 2048;
+}
+
+// The box of wide tiles whose halo reaches the block (the kernels'
+// halo_near_block): one axis at a time.
+void near_block(CaseDev& h)
+{
+    if (!h.has_block) return;
+    const int n[3] = {h.wide.ntx, h.wide.nty, h.wide.ntz}, ext[3] = {WideTile::TX, WideTile::TY, WideTile::TZ};
+    int64_t count = 1;
+    for (int a = 0; a < 3; ++a) {
+        for (int k = 0; k < n[a]; ++k)
+            if (k * ext[a] - 1 < h.blk_hi[a] && (k + 1) * ext[a] + 1 > h.blk_lo[a]) {
+                if (!h.near_n[a]) h.near_lo[a] = k;
+                ++h.near_n[a];
+            }
+        count *= h.near_n[a];
+    }
+    const int subs = (WideTile::TY / Model<3>::TY) * (WideTile::TZ / Model<3>::TZ);
+    h.near_subs = (int32_t)(((count * subs + 7) / 8) * 8);
+}
+
 // Codec constants.  FP16 stores h_j - w_j phi (phi of the reading node one
 // step earlier) times 2^14 and g times 2^12; the stored values are small
 // (|h_j - w_j phi| < w_j, |g_i| of the order of w_i |u| / T), so the scales
@@ -334,6 +380,14 @@ void derived_constants(CaseDev& h)
     f.g_inv_scale = (float)h.g_inv_scale;
 }
 
+// Kernel `which` of a single case at step offset off (parity: of that step).
+void launch_case(pulbm_case* c, int off, int which, int parity)
+{
+    const int ls = lattice_set(c->p.dim, c->p.q_hydro);
+    if (c->nwide && (which == 1 || which == 2)) launch_wide(ls, c->stream, c->tab, c->h.near_subs + grid_of(c->nwide), off, which);
+    else launch(ls, c->p.store, c->p.collision == 1, c->stream, c->tab, c->hdr, grid_of(c->ntiles), off, which, parity, c->lds);
+}
+
 int upload_desc(pulbm_case* c)
 {
     HIPC(hipMemcpyAsync(c->d, &c->h, sizeof(CaseDev), hipMemcpyHostToDevice, c->stream));
@@ -347,7 +401,7 @@ int upload_desc(pulbm_case* c)
 int read_pass(pulbm_case* c)
 {
     for (int w = 0; w < kReadKernels; ++w)
-        launch(lattice_set(c->p.dim, c->p.q_hydro), c->p.store, c->p.collision == 1, c->stream, c->tab, c->hdr, grid_of(c->ntiles), -1, w);
+        launch_case(c, -1, w, 0);
     HIPC(hipGetLastError());
     return PULBM_OK;
 }
@@ -430,15 +484,17 @@ extern "C" int pulbm_create(const pulbm_params* p, void* dev_arena, size_t arena
     std::memset(&h, 0, sizeof h);
     h.nx = p->nx; h.ny = p->ny; h.nz = p->nz; h.dim = p->dim;
     for (int a = 0; a < 3; ++a) { h.wall[a] = p->wall[a]; h.grav[a] = p->gravity[a]; }
-    if (p->dim == 2) tiles_of<2>(*p, &h.ntx, &h.nty, &h.ntz);
-    else tiles_of<3>(*p, &h.ntx, &h.nty, &h.ntz);
-    c->ntiles = h.ntx * h.nty * h.ntz;
     // y bands of at least 64 tiles per z layer, and of 16 tile rows while a
     // layer's band stays within 128 tiles: z neighbours then run within what
     // one XCD holds at once (measured against plain x-y-z order: 128^3 +1%,
     // 256^3 +6%; 16 rows rather than 8 on the 512-wide dam break: +1.7%)
-    h.tband = std::max(4, std::min(32, std::max(64 / h.ntx, std::min(16, 128 / h.ntx))));
-    tile_divisors(h, c->ntiles);
+    static_assert(Model<2>::TX == 64 && Model<3>::TX == 64 && WideTile::TX == 64, "one tile width");
+    const int ntx = (p->nx + 63) / 64;
+    const int tband = std::max(4, std::min(32, std::max(64 / ntx, std::min(16, 128 / ntx))));
+    h.map = p->dim == 2 ? tile_map<Model<2>>(*p, tband) : tile_map<Model<3>>(*p, tband);
+    c->ntiles = h.map.ntx * h.map.nty * h.map.ntz;
+    // the wide tiles' rows are twice as high
+    if (p->dim == 3) h.wide = tile_map<WideTile>(*p, tband / 2);
     h.delta_theta = p->delta_theta;
     h.sx = row_pitch(p->nx);
     h.N = (int64_t)h.sx * p->ny * p->nz;
@@ -463,6 +519,10 @@ extern "C" int pulbm_create(const pulbm_params* p, void* dev_arena, size_t arena
     for (int a = 0; a < 3; ++a) {
         h.blk_lo[a] = h.has_block ? p->block_lo[a] : 0;
         h.blk_hi[a] = h.has_block ? p->block_hi[a] : 0;
+    }
+    if (wide_tiles(*p, c->ntiles)) {
+        c->nwide = h.wide.ntx * h.wide.nty * h.wide.ntz;
+        near_block(h);
     }
     // the collide kernel rebuilds u from a 2-node halo of the new P where
     // every tile is clear of walls, the open end and the block, and one
@@ -553,8 +613,7 @@ static void queue_direct(pulbm_case* c, int64_t first, int count)
     for (int k = 0; k < count; ++k)
         for (int w = 0; w < kStepKernels; ++w)
             if (w != kVelocityKernel || !c->h.fuse_u)
-                launch(lattice_set(c->p.dim, c->p.q_hydro), c->p.store, c->p.collision == 1, c->stream, c->tab,
-                       c->hdr, grid_of(c->ntiles), k, w, (int)((first + k) & 1), c->lds);
+                launch_case(c, k, w, (int)((first + k) & 1));
     hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, c->stream, c->tab, c->hdr, count);
 }
 
@@ -591,8 +650,7 @@ extern "C" int pulbm_step_timed(pulbm_case* c, int64_t nsteps, double* ms)
         (void)hipEventRecord(ev[0], c->stream);
         for (int w = 0; w < kStepKernels; ++w) {
             if (w != kVelocityKernel || !c->h.fuse_u)
-                launch(lattice_set(c->p.dim, c->p.q_hydro), c->p.store, c->p.collision == 1, c->stream, c->tab,
-                       c->hdr, grid_of(c->ntiles), 0, w, (int)(c->step & 1), c->lds);
+                launch_case(c, 0, w, (int)(c->step & 1));
             (void)hipEventRecord(ev[w + 1], c->stream);
         }
         hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, c->stream, c->tab, c->hdr, 1);
