@@ -18,9 +18,12 @@
 //              differences of phi, rho and u, the BGK phase-field collision
 //              and the filter collision of the hydrodynamic LBE, written back
 //              in place (AA pattern).  Cases without walls, open end or block
-//              on D3Q19 or D2Q9 hydro (with 4- or 8-byte storage) rebuild u
-//              here from u* and a 2-node halo of the new P, and a step skips
-//              k_velocity.
+//              on D3Q19 hydro (with 4- or 8-byte storage) rebuild u here from
+//              u* and a 2-node halo of the new P, and a step skips k_velocity;
+//              2D cases rebuild P as well (from a 3-node halo of P* and u*),
+//              and a step is k_moments and k_collide alone.
+// Large single 3D cases take pressure and velocity on wide tiles
+// (k_pressure_wide, k_velocity_wide).
 //
 // Memory layout (per case): structure of arrays, x fastest; population i of
 // node n at f[i*N + n].  AA pattern: on even steps node x reads slot i of x
@@ -97,7 +100,9 @@ struct CaseDev {
     int32_t has_block;
     int32_t fuse_u; // 1: the collide kernel rebuilds u itself and a step skips k_velocity
                     // (no wall, open end or block, 4- or 8-byte storage, every axis >= 3,
-                    // D2Q9 or D3Q19 hydro)
+                    // D3Q19 hydro)
+                    // 2: it rebuilds P and u, and a step skips k_pressure and k_velocity
+                    // (2D, no block, both axes >= 3)
     int32_t tile_rev;  // 1: the case's tiles are taken in reverse order (a race check, pulbm_set_tile_order)
     int32_t nt_odd_moments;  // 1: k_moments streams its 4- and 8-byte loads on odd steps too
     // Constants of the collision derived once on the host (so no thread
@@ -585,12 +590,14 @@ template <class CT, int NF, int NC> struct Cells {
     }
 };
 
-// 1-halo region of a tile: cell k -> mirror node index, wall offsets, crossings.
-template <class Mo, int DIMV>
-struct Halo1 {
-    static constexpr int D = 1;  // halo depth
-    static constexpr int ZH = DIMV == 3 ? 1 : 0;
-    static constexpr int RX = Mo::TX + 2, RY = Mo::TY + 2, RZ = Mo::TZ + 2 * ZH;
+// Halo region of a tile, DH nodes deep: cell k -> mirror node index, wall
+// offsets, crossings.  (Cells two and more beyond a wall or the open end, and
+// inside the block behind its faces, hold values that no node uses.)
+template <class Mo, int DIMV, int DH>
+struct HaloN {
+    static constexpr int D = DH;  // halo depth
+    static constexpr int ZH = DIMV == 3 ? DH : 0;
+    static constexpr int RX = Mo::TX + 2 * DH, RY = Mo::TY + 2 * DH, RZ = Mo::TZ + 2 * ZH;
     using R = Region<RX, RY, RZ>;
     static constexpr bool VEC = false;  // LDS cells are written one by one
     __device__ static __forceinline__ int slot(int k) { return k; }
@@ -602,8 +609,8 @@ struct Halo1 {
         const int ix = k % RX, iy = (k / RX) % RY, iz = k / (RX * RY);
         *cr = 0;
         int m[3];
-        m[0] = resolve_axis(t.ox - 1 + ix, cs.nx, cs.wall[0], &off[0], cr);
-        m[1] = resolve_axis(t.oy - 1 + iy, cs.ny, cs.wall[1], &off[1], cr);
+        m[0] = resolve_axis(t.ox - DH + ix, cs.nx, cs.wall[0], &off[0], cr);
+        m[1] = resolve_axis(t.oy - DH + iy, cs.ny, cs.wall[1], &off[1], cr);
         m[2] = resolve_axis(t.oz - ZH + iz, cs.nz, cs.wall[2], &off[2], cr);
         if (BND && in_block(cs, m[0], m[1], m[2])) {
             // a block node mirrors across each exposed face it lies on
@@ -624,6 +631,8 @@ struct Halo1 {
         return (uint32_t)m[0] + (uint32_t)cs.sx * ((uint32_t)m[1] + (uint32_t)cs.ny * (uint32_t)m[2]);
     }
 };
+
+template <class Mo, int DIMV> using Halo1 = HaloN<Mo, DIMV, 1>;
 
 // 2-halo region of a tile on a grid without walls, open end or block and
 // with every axis of at least 3 nodes, so that one +-n wraps a coordinate
@@ -697,7 +706,6 @@ __device__ __forceinline__ void halo_rows(CDesc& cs, const TileCtx& t, void* con
     constexpr int NVEC = ROWS * LPR, NEDGE = 2 * DH * ROWS;
     constexpr int PV = (NVEC + 255) / 256, PE = (NEDGE + 255) / 256;
     static_assert(TX % 4 == 0, "rows of 4-element vectors");
-    static_assert(!WALL || DH == 1, "walls mirror one ghost layer");
     typedef CT V4 __attribute__((ext_vector_type(4)));
     const int tid = (int)threadIdx.x;
     // node index of the start of halo row r, its first LDS cell, and (at
@@ -1366,6 +1374,8 @@ __global__ __launch_bounds__(256) void k_pressure(CaseTab cases, const int* hdr,
     const TileCtx t = tile_ctx<Mo>(cases, hdr, step_off);
     if (!t.active) return;
     CDesc& cs = *t.cs;
+    // a fused case's collide rebuilds P itself; the read pass (step_off < 0) still needs it here
+    if (cs.fuse_u == 2 && step_off >= 0) return;
     if (tile_at_wall<Mo>(cs, t.ox, t.oy, t.oz)) pressure_tile<LS, AT, true, R>(cs, t, sP, sGD, sJ);
     else pressure_tile<LS, AT, false, R>(cs, t, sP, sGD, sJ);
 }
@@ -1838,11 +1848,164 @@ template <int LS, class S>
 using TileCells = Cells<typename Codec<S>::CT, CellF<Model<LS>::DIM>::NF, Halo1<Model<LS>, Model<LS>::DIM>::R::N>;
 
 // Does a lattice set's collide kernel rebuild u for some cases (CaseDev::fuse_u)?
-template <int LS, class S> constexpr bool can_fuse_u() { return LS != 3 && sizeof(S) >= 4; }
+template <int LS, class S> constexpr bool can_fuse_u() { return LS == 4 && sizeof(S) >= 4; }
+
+// --- pressure and velocity of a 2D tile inside its collide kernel (CaseDev::fuse_u
+// 2).  A 2D step on the grids it is run on is bound by the latency of its
+// launches, about 4.7 us each (200 x 400: 19.4 us a step for four kernels), not
+// by their work, so a tile takes P* and u* three nodes deep and forms P two and
+// u one node deep itself (2.1 and 1.5 times its 256 nodes), each value by
+// k_pressure's and k_velocity's expressions, term by term.  A ghost beyond a wall
+// or the open end is formed at its mirror node, inward in the same region.  (A
+// block's ghosts mirror outward, past the region: cases with a block keep the
+// separate kernels.)
+template <class S> struct Flow2D {
+    using CT = typename Codec<S>::CT;
+    using H3 = HaloN<Model<2>, 2, 3>;
+    Cells<CT, 4, H3::R::N> f;  // P*, u*, phi
+    CT gd[H3::R::N];           // g . (ghost - mirror)
+    CT P[Halo2<Model<2>, 2>::R::N];
+};
+
+// The node that a 2D cell beyond a wall or the open end mirrors: (x - dx, y - dy).
+struct Mirror {
+    int dx, dy;
+    bool odd, open;
+};
+template <bool WALL> __device__ __forceinline__ Mirror mirror(CDesc& cs, int x, int y)
+{
+    Mirror m = {0, 0, false, false};
+    if constexpr (WALL) {
+        int cr = 0;
+        (void)resolve_axis(x, cs.nx, cs.wall[0], &m.dx, &cr);
+        (void)resolve_axis(y, cs.ny, cs.wall[1], &m.dy, &cr);
+        m.odd = cr & 1;
+        m.open = cr & kOpenGhost;
+    }
+    return m;
+}
+
+template <class S, bool WALL>
+__device__ __forceinline__ void rebuild_2d(CDesc& cs, const TileCtx& t, TileCells<2, S>& sC, Flow2D<S>& s, int lx,
+                                           int ly, typename Codec<S>::CT* Pown)
+{
+    using CT = typename Codec<S>::CT;
+    using G = D2Q9;
+    using F = CellF<2>;
+    using Mo = Model<2>;
+    using H3 = HaloN<Mo, 2, 3>;
+    using H2 = Halo2<Mo, 2>;
+    using H1 = Halo1<Mo, 2>;
+    const Slots<CT> Js = slots<CT>(cs.J, cs.N);
+    void* src[4] = {cs.Ps, (void*)Js.at(0, 0), (void*)Js.at(1, 0), cs.phi[t.step & 1]};
+    halo_stage<H3, WALL, 4, CT, true>(cs, t, src, [&](int k, int cr, const int* off, const CT* v) {
+        CT c[4] = {v[0], v[1], v[2], v[3]}, gd = 0;
+        if (WALL) gd = (CT)(cs.grav[0] * off[0] + cs.grav[1] * off[1] + cs.grav[2] * off[2]);
+        if (WALL && (cr & kOpenGhost)) {
+            c[0] = (CT)(2.0 * cs.p_top - (double)c[0]);
+            gd = 0;
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+            if (WALL && (cr & 1)) c[1 + a] = (CT)(-(double)c[1 + a] + 2.0 * cs.grav[a]);
+        s.f.put(k, c);
+        if (WALL) s.gd[k] = gd;
+    });
+    __syncthreads();
+    // (cells past a region repeat its last one: every pass's cells are in flight
+    // together)
+    // P two nodes deep
+    constexpr int N2 = H2::R::N, N1 = H1::R::N;
+#pragma unroll
+    for (int it = 0; it < (N2 + 255) / 256; ++it) {
+        const int k = min((int)threadIdx.x + 256 * it, N2 - 1), ix = k % H2::RX, iy = k / H2::RX;
+        const Mirror m2 = mirror<WALL>(cs, t.ox - 2 + ix, t.oy - 2 + iy);
+        const int k3 = H3::R::idx(ix + 1 - m2.dx, iy + 1 - m2.dy, 0);
+        auto cell = [&](int i, int sgn, CT* v) {
+            const int m = k3 + sgn * (G::c(i, 0) + H3::RX * G::c(i, 1));
+            s.f.get({m * 16, m * (int)sizeof(CT)}, 0, v);
+        };
+        CT c0[4];
+        cell(0, 1, c0);
+        const double drho = (double)clamp01(c0[3]) * (cs.rho_w - cs.rho_a);
+        const double rho = cs.rho_a + drho;
+        constexpr int NS = shell<G>(G::Q - 1) + 1;
+        CT sks[NS], sgs[NS], dus[2][NS];
+#pragma unroll
+        for (int h = 0; h < NS; ++h) sks[h] = sgs[h] = dus[0][h] = dus[1][h] = 0;
+#pragma unroll
+        for (int i = 1; i < G::Q; i += 2) {
+            const int h = shell<G>(i);
+            CT m[4], p[4];
+            cell(i, -1, m);
+            cell(i, 1, p);
+            sks[h] += (m[0] - c0[0]) + (p[0] - c0[0]);
+            if (WALL) {
+                const int o = G::c(i, 0) + H3::RX * G::c(i, 1);
+                sgs[h] += s.gd[k3 - o] + s.gd[k3 + o];
+            }
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                if (G::c(i, a) == 0) continue;
+                const CT d = m[1 + a] - p[1 + a];
+                if (G::c(i, a) == 1) dus[a][h] += d;
+                else dus[a][h] -= d;
+            }
+        }
+        double sk = 0, sg = 0, su = 0;
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+            const double w = shell_w<G>(h);
+            sk += w * (double)sks[h];
+            if (WALL) sg += w * (double)sgs[h];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) su += w * (double)dus[a][h];
+        }
+        if (WALL) sk += rho * sg;
+        CT P = (CT)((double)c0[0] + (sk + drho * su));
+        if (WALL && m2.open) P = (CT)(2.0 * cs.p_top - (double)P);
+        s.P[k] = P;
+    }
+    __syncthreads();
+    *Pown = s.P[H2::R::idx(lx + 2, ly + 2, 0)];
+    // u one node deep
+    const CT ra = cconst<CT>(cs.rho_a, cs.f32.rho_a), dr = cconst<CT>(cs.rho_w - cs.rho_a, cs.f32.drho);
+#pragma unroll
+    for (int it = 0; it < (N1 + 255) / 256; ++it) {
+        const int k = min((int)threadIdx.x + 256 * it, N1 - 1), ix = k % H1::RX, iy = k / H1::RX;
+        const Mirror m1 = mirror<WALL>(cs, t.ox - 1 + ix, t.oy - 1 + iy);
+        const int k2 = H2::R::idx(ix + 1 - m1.dx, iy + 1 - m1.dy, 0), k3 = H3::R::idx(ix + 2 - m1.dx, iy + 2 - m1.dy, 0);
+        CT c[4], f[F::NF];
+        s.f.get({k3 * 16, k3 * (int)sizeof(CT)}, 0, c);
+        const CT rho = ra + clamp01(c[3]) * dr;
+        const CT irho = rcp(rho);
+        CT gr[2] = {0, 0};
+#pragma unroll
+        for (int i = 1; i < G::Q; i += 2) {
+            const int o2 = G::c(i, 0) + H2::RX * G::c(i, 1), o3 = G::c(i, 0) + H3::RX * G::c(i, 1);
+            const CT p = s.P[k2 + o2], m = s.P[k2 - o2];
+            const CT d = (WALL ? (p + rho * s.gd[k3 + o3]) - (m + rho * s.gd[k3 - o3]) : p - m) * (CT)G::w(i);
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                if (G::c(i, a) == 1) gr[a] += d;
+                if (G::c(i, a) == -1) gr[a] -= d;
+            }
+        }
+        f[F::PHI] = c[3];
+        f[F::RHO] = rho;
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            const CT u = c[1 + a] - gr[a] * (CT)3.0 * irho;
+            f[F::U + a] = m1.odd ? -u : u;  // no slip
+        }
+        sC.put(k, f);
+    }
+    __syncthreads();
+}
 
 template <int LS, class S, bool WALL, bool BGK, class R, int PAR>
 __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCells<LS, S>& sC, S (*sH)[256],
-                                             typename Codec<S>::CT* sP2)
+                                             typename Codec<S>::CT* sP2, Flow2D<S>* s2)
 {
     constexpr int DIMV = Model<LS>::DIM;
     using Mo = Model<LS>;
@@ -1891,9 +2054,7 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCe
 #pragma unroll
         for (int j = 0; j < H::Q; ++j) hraw[j] = aa_load<H, WALL, nt_access<S, kLoadCollide>()>(hs, nb, nv, j, odd);
         if constexpr (BGK) {
-            dP = (CT)(((double)*at_node<CT>(cs.P[t.step & 1], n) - (double)*at_node<CT>(cs.P[(t.step + 1) & 1], n)) *
-                      (3.0 / cs.rho_a));
-            asm("" : "+v"(dP));
+            dP = *at_node<CT>(cs.P[t.step & 1], n);  // the previous P; the new one below
         } else {
             const Slots<M2L> Ms = slots<M2L>(cs.M2, cs.N);
 #pragma unroll
@@ -1906,21 +2067,34 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCe
     // itself below
     bool fused = false;
     if constexpr (!WALL && can_fuse_u<LS, S>()) fused = cs.fuse_u;
-    const Slots<CT> Us = slots<CT>(fused ? cs.J : cs.U[t.step & 1], cs.N);
-    void* src[1 + DIMV];
-    src[0] = cs.phi[t.step & 1];
+    const bool fused2d = LS == 2 && cs.fuse_u == 2;
+    CT Pnew = 0;
+    if constexpr (LS == 2) {
+        if (fused2d) {
+            // ghosts show in the 3-node halo of a tile up to two nodes clear of a wall
+            if (WALL || (cs.wall[0] && t.ox + Mo::TX + 2 >= cs.nx) || (cs.wall[1] && t.oy + Mo::TY + 2 >= cs.ny))
+                rebuild_2d<S, true>(cs, t, sC, *s2, lx, ly, &Pnew);
+            else
+                rebuild_2d<S, false>(cs, t, sC, *s2, lx, ly, &Pnew);
+        }
+    }
+    if (!fused2d) {
+        const Slots<CT> Us = slots<CT>(fused ? cs.J : cs.U[t.step & 1], cs.N);
+        void* src[1 + DIMV];
+        src[0] = cs.phi[t.step & 1];
 #pragma unroll
-    for (int a = 0; a < DIMV; ++a) src[1 + a] = (void*)Us.at(a, 0);
-    halo_stage<HR, WALL, 1 + DIMV, CT, true>(
-        cs, t, src,
-        [&](int k, int cr, const int*, const CT* v) {
-            CT f[F::NF];
-            f[F::PHI] = v[0];
-            f[F::RHO] = ph.rho_a + clamp01(v[0]) * ph.drho;
+        for (int a = 0; a < DIMV; ++a) src[1 + a] = (void*)Us.at(a, 0);
+        halo_stage<HR, WALL, 1 + DIMV, CT, true>(
+            cs, t, src,
+            [&](int k, int cr, const int*, const CT* v) {
+                CT f[F::NF];
+                f[F::PHI] = v[0];
+                f[F::RHO] = ph.rho_a + clamp01(v[0]) * ph.drho;
 #pragma unroll
-            for (int a = 0; a < DIMV; ++a) f[F::U + a] = (WALL && (cr & 1)) ? -v[1 + a] : v[1 + a];  // no slip
-            sC.put(k, f);
-        });
+                for (int a = 0; a < DIMV; ++a) f[F::U + a] = (WALL && (cr & 1)) ? -v[1 + a] : v[1 + a];  // no slip
+                sC.put(k, f);
+            });
+    }
     if constexpr (!WALL && can_fuse_u<LS, S>()) {
         if (fused) {
             void* psrc[1] = {cs.P[(t.step + 1) & 1]};
@@ -1978,7 +2152,24 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCe
             __syncthreads();
         }
     }
+    if constexpr (LS == 2) {
+        // the new P and u of the tile's own nodes
+        if (fused2d && inside) {
+            CT f[F::NF];
+            const int c = R::idx(lx + 1, ly + 1, 0);
+            sC.get({c * 16, c * (int)sizeof(CT)}, 0, f);
+            *at_node<CT>(cs.P[(t.step + 1) & 1], n) = Pnew;
+            const Slots<CT> Un = slots<CT>(cs.U[t.step & 1], cs.N);
+#pragma unroll
+            for (int a = 0; a < DIMV; ++a) *Un.at(a, n * (uint32_t)sizeof(CT)) = f[F::U + a];
+        }
+    }
     if (!inside) return;
+    if constexpr (BGK) {
+        if (!fused2d) Pnew = *at_node<CT>(cs.P[(t.step + 1) & 1], n);
+        dP = (CT)(((double)dP - (double)Pnew) * (3.0 / cs.rho_a));
+        asm("" : "+v"(dP));
+    }
 
     CT m2[NM];
     if constexpr (!BGK) {
@@ -2157,17 +2348,20 @@ __global__ __launch_bounds__(256) PULBM_COLLIDE_ATTR void k_collide(CaseTab case
     __shared__ S sH[sizeof(S) == 2 ? 1 : H::Q][256];
     // the new P two nodes deep, for cases whose collide rebuilds u
     __shared__ CT sP2[can_fuse_u<LS, S>() ? Halo2<Mo, DIMV>::R::N : 1];
+    // P*, u* and the new P of a 2D tile, for cases whose collide rebuilds both
+    struct None {};
+    __shared__ std::conditional_t<LS == 2, Flow2D<S>, None> s2;
     const TileCtx t = tile_ctx<Mo>(cases, hdr, step_off);
     if (!t.active || (int)(t.step & 1) != PAR) return;
     CDesc& cs = *t.cs;
     if (tile_at_wall<Mo>(cs, t.ox, t.oy, t.oz)) {
-        collide_tile<LS, S, true, BGK, R, PAR>(cs, t, sC, sH, sP2);
+        collide_tile<LS, S, true, BGK, R, PAR>(cs, t, sC, sH, sP2, (Flow2D<S>*)&s2);
     } else if (PAR == 1 && t.ox >= 1 && t.ox + Mo::TX < cs.nx && t.oy >= 1 && t.oy + Mo::TY < cs.ny &&
                (DIMV == 2 || (t.oz >= 1 && t.oz + Mo::TZ < cs.nz))) {
         // every node of the tile has its neighbours inside the grid
-        collide_tile<LS, S, false, BGK, R, 2>(cs, t, sC, sH, sP2);
+        collide_tile<LS, S, false, BGK, R, 2>(cs, t, sC, sH, sP2, (Flow2D<S>*)&s2);
     } else {
-        collide_tile<LS, S, false, BGK, R, PAR>(cs, t, sC, sH, sP2);
+        collide_tile<LS, S, false, BGK, R, PAR>(cs, t, sC, sH, sP2, (Flow2D<S>*)&s2);
     }
 }
 

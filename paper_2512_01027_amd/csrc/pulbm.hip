@@ -183,7 +183,9 @@ template <class Tile> TileMap tile_map(const pulbm_params& p, int tband)
 int grid_of(int tiles) { return ((tiles + 7) / 8) * 8; }
 
 constexpr int kStepKernels = 4;  // moments, pressure, velocity, collide + stream
-constexpr int kVelocityKernel = 2;
+constexpr int kPressureKernel = 1, kVelocityKernel = 2;
+// Does a step of a case run kernel w (CaseDev::fuse_u)?
+bool step_runs(int fuse_u, int w) { return !((w == kVelocityKernel && fuse_u) || (w == kPressureKernel && fuse_u == 2)); }
 constexpr int kReadKernels = 3;  // the moment stage only
 
 }  // namespace
@@ -527,11 +529,18 @@ extern "C" int pulbm_create(const pulbm_params* p, void* dev_arena, size_t arena
     // the collide kernel rebuilds u from a 2-node halo of the new P where
     // every tile is clear of walls, the open end and the block, and one
     // +-n wraps two nodes past either end of every axis.  Measured at 128^3:
-    // with D3Q19 and D2Q9 hydro (9 and 4 direction pairs) this saves more
-    // than it adds to the collide kernel; with D3Q27 (13 pairs) the two
-    // cancel, and the separate velocity kernel is kept.
+    // with D3Q19 hydro (9 direction pairs) this saves more than it adds to the
+    // collide kernel; with D3Q27 (13 pairs) the two cancel, and the separate
+    // velocity kernel is kept.
     h.fuse_u = !h.has_block && !p->wall[0] && !p->wall[1] && !p->wall[2] && store_bytes(p->store) >= 4 &&
-               p->nx >= 3 && p->ny >= 3 && (p->dim == 2 || (p->nz >= 3 && p->q_hydro == 19));
+               p->nx >= 3 && p->ny >= 3 && p->dim == 3 && p->nz >= 3 && p->q_hydro == 19;
+    // in 2D it rebuilds P and u (rebuild_2d), where one +-n wraps three nodes
+    // past either end of both axes.  Measured against the separate kernels, step:
+    // 64^2 FP64 13.8 / 11.4 us, 200 x 400 with walls FP32 19.4 / 15.4 us, 300^2
+    // FP16 17.4 / 11.7 us, 1024^2 FP16 55 / 45 us, 1000 x 600 FP64 78 / 74 us:
+    // every size gains, the small ones two launches, the large ones the fields
+    // that no longer pass through memory.
+    if (p->dim == 2 && !h.has_block && p->nx >= 3 && p->ny >= 3) h.fuse_u = 2;
     codec_constants(*p, h);
     derived_constants(h);
     c->lds = collide_lds(*p, h.N);
@@ -612,8 +621,7 @@ static void queue_direct(pulbm_case* c, int64_t first, int count)
 {
     for (int k = 0; k < count; ++k)
         for (int w = 0; w < kStepKernels; ++w)
-            if (w != kVelocityKernel || !c->h.fuse_u)
-                launch_case(c, k, w, (int)((first + k) & 1));
+            if (step_runs(c->h.fuse_u, w)) launch_case(c, k, w, (int)((first + k) & 1));
     hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, c->stream, c->tab, c->hdr, count);
 }
 
@@ -649,8 +657,7 @@ extern "C" int pulbm_step_timed(pulbm_case* c, int64_t nsteps, double* ms)
     for (int64_t s = 0; s < nsteps && rc == PULBM_OK; ++s) {
         (void)hipEventRecord(ev[0], c->stream);
         for (int w = 0; w < kStepKernels; ++w) {
-            if (w != kVelocityKernel || !c->h.fuse_u)
-                launch_case(c, 0, w, (int)(c->step & 1));
+            if (step_runs(c->h.fuse_u, w)) launch_case(c, 0, w, (int)(c->step & 1));
             (void)hipEventRecord(ev[w + 1], c->stream);
         }
         hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, c->stream, c->tab, c->hdr, 1);
@@ -1054,7 +1061,9 @@ struct pulbm_batch {
         hipEvent_t staged[2] = {nullptr, nullptr};
         int which = 0;
         int cap = 0, ncases = 0, tiles = 0, grid = 0;
-        std::map<int, hipGraphExec_t> graphs;  // by 4 ksteps + parity (0, 1; 2 mixed), captured for `grid` blocks
+        int kernels = 0;  // bit w: some case's step runs kernel w
+        // by 64 ksteps + 16 parity (0, 1; 2 mixed) + kernels, captured for `grid` blocks
+        std::map<int, hipGraphExec_t> graphs;
     } tab[6];  // index (lattice set - 2) + 3 * collision
     bool dirty = true;
 };
@@ -1160,9 +1169,11 @@ int rebuild_tables(pulbm_batch* b)
         int* hdr = (int*)(t.stage[t.which] + t.cap * sizeof(CaseDev*));
         int n = 0;
         hdr[2] = 0;
+        t.kernels = 0;
         for (auto& s : b->slots)
             if (s.c && lattice_set(s.c->p.dim, s.c->p.q_hydro) == ls && s.c->p.collision == coll) {
                 ptr[n] = s.c->d;
+                for (int w = 0; w < kStepKernels; ++w) t.kernels |= step_runs(s.c->h.fuse_u, w) ? 1 << w : 0;
                 hdr[3 + n] = hdr[2 + n] + s.c->ntiles;
                 ++n;
             }
@@ -1294,7 +1305,7 @@ extern "C" int pulbm_batch_advance(pulbm_batch* b, int32_t ksteps)
                 par = par == -2 ? p : (par == p ? p : -1);
             }
         if (par == -2) par = 0;
-        const int key = ksteps * 4 + (par < 0 ? 2 : par);
+        const int key = ksteps * 64 + (par < 0 ? 2 : par) * 16 + t.kernels;
         auto it = t.graphs.find(key);
         if (it == t.graphs.end()) {
             hipGraph_t g = nullptr;
@@ -1302,8 +1313,9 @@ extern "C" int pulbm_batch_advance(pulbm_batch* b, int32_t ksteps)
             HIPC(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
             for (int k = 0; k < ksteps; ++k)
                 for (int w = 0; w < kStepKernels; ++w)
-                    launch(di % 3 + 2, b->store, di / 3 == 1, b->stream, t.dtab, t.dhdr, t.grid, k, w,
-                           par < 0 ? -1 : (par + k) & 1);
+                    if (t.kernels & 1 << w)
+                        launch(di % 3 + 2, b->store, di / 3 == 1, b->stream, t.dtab, t.dhdr, t.grid, k, w,
+                               par < 0 ? -1 : (par + k) & 1);
             hipLaunchKernelGGL(k_advance, dim3((t.cap + 63) / 64), dim3(64), 0, b->stream, t.dtab, t.dhdr, ksteps);
             HIPC(hipStreamEndCapture(b->stream, &g));
             HIPC(hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
