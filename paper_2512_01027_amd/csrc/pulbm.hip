@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -14,6 +15,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "kernels.hpp"
@@ -190,6 +192,75 @@ constexpr int kReadKernels = 3;  // the moment stage only
 
 }  // namespace
 
+namespace {
+
+// Pinned pieces that a read-back passes through.  They outlive a read (a
+// pinned allocation costs 60 us, a 64^2 read 60 us): up to kPinKeep of them wait
+// in one list for the next read of any case, thread or device, and the last
+// case or batch to go (PinUser) gives them back.
+constexpr size_t kPinBytes = size_t(1) << 20;
+constexpr int kPinKeep = 16;
+struct {
+    std::mutex lock;
+    char* idle[kPinKeep];
+    int n = 0, users = 0;
+} g_pins;
+
+char* pin_take()
+{
+    {
+        std::lock_guard<std::mutex> hold(g_pins.lock);
+        if (g_pins.n) return g_pins.idle[--g_pins.n];
+    }
+    // (another stream of the caller's may be under capture)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    char* p = nullptr;
+    if (hipHostMalloc((void**)&p, kPinBytes, hipHostMallocPortable) != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return p;
+}
+
+void pin_give(char* p)
+{
+    if (!p) return;
+    {
+        std::lock_guard<std::mutex> hold(g_pins.lock);
+        if (g_pins.n < kPinKeep) {
+            g_pins.idle[g_pins.n++] = p;
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
+// Held by every case and batch.
+struct PinUser {
+    PinUser()
+    {
+        std::lock_guard<std::mutex> hold(g_pins.lock);
+        ++g_pins.users;
+    }
+    ~PinUser()
+    {
+        char* gone[kPinKeep];
+        int n = 0;
+        {
+            std::lock_guard<std::mutex> hold(g_pins.lock);
+            if (--g_pins.users == 0)
+                while (g_pins.n) gone[n++] = g_pins.idle[--g_pins.n];
+        }
+        while (n) (void)hipHostFree(gone[--n]);
+    }
+    PinUser(const PinUser&) = delete;
+    PinUser& operator=(const PinUser&) = delete;
+};
+
+}  // namespace
+
 struct pulbm_case {
     pulbm_params p;
     hipStream_t stream = nullptr;
@@ -206,6 +277,7 @@ struct pulbm_case {
     int64_t step = 0;
     bool ready = false;
     int device = 0;           // device current at pulbm_create
+    PinUser pins;
 };
 
 // ------------------------------------------------------------ dispatch
@@ -405,31 +477,6 @@ int read_pass(pulbm_case* c)
     for (int w = 0; w < kReadKernels; ++w)
         launch_case(c, -1, w, 0);
     HIPC(hipGetLastError());
-    return PULBM_OK;
-}
-
-// Padded device rows of sx values -> compact host rows of nx doubles.
-template <class AT>
-void to_double(const std::vector<char>& raw, double* out, size_t rows, size_t nx, size_t sx)
-{
-    const AT* src = (const AT*)raw.data();
-    for (size_t r = 0; r < rows; ++r)
-        for (size_t i = 0; i < nx; ++i) out[r * nx + i] = (double)src[r * sx + i];
-}
-
-// Copy `comps` fields (each of N padded nodes) from the device into compact
-// host rows of nx doubles: one contiguous copy (a strided copy to pageable
-// memory goes row by row), then the rows are compacted on the host.
-int fetch(pulbm_case* c, const void* dev, double* out, int comps)
-{
-    if (!out) return PULBM_OK;
-    const size_t ab = aux_bytes(c->p.store);
-    const size_t nx = (size_t)c->p.nx, sx = (size_t)c->h.sx, rows = (size_t)comps * c->p.ny * c->p.nz;
-    std::vector<char> raw(rows * sx * ab);
-    HIPC(hipMemcpyAsync(raw.data(), dev, raw.size(), hipMemcpyDeviceToHost, c->stream));
-    HIPC(hipStreamSynchronize(c->stream));
-    if (ab == 8) to_double<double>(raw, out, rows, nx, sx);
-    else to_double<float>(raw, out, rows, nx, sx);
     return PULBM_OK;
 }
 
@@ -680,16 +727,142 @@ extern "C" int pulbm_step_timed(pulbm_case* c, int64_t nsteps, double* ms)
     return rc;
 }
 
+namespace {
+
+// A field's components on the device (padded rows of sx values in the auxiliary
+// type) and on the host (compact rows of nx doubles).
+constexpr int kMaxComps = 5;
+struct ReadBack {
+    const void* dev[kMaxComps];
+    double* host[kMaxComps];
+    int comps = 0;
+};
+template <class AT> struct PackSrc { const AT* f[kMaxComps]; };
+
+// `count` compact values from component f0, row row0, column i0 on, into pinned
+// host memory.  Bound by the link to the host (about 55 GB/s for 1 MiB pieces,
+// what a copy reaches); written by a kernel, as the rows' padding falls away
+// and one launch serves all fields of a small case.
+template <class AT>
+__global__ __launch_bounds__(256) void k_pack_rows(PackSrc<AT> src, int f0, uint32_t row0, uint32_t i0, uint32_t rows,
+                                                   uint32_t nx, uint32_t sx, uint32_t count, AT* __restrict__ out)
+{
+    for (uint32_t k = blockIdx.x * 256 + threadIdx.x; k < count; k += gridDim.x * 256) {
+        const uint32_t e = i0 + k;
+        uint32_t r = row0 + e / nx;
+        int f = f0;
+        for (; r >= rows; r -= rows) ++f;
+        out[k] = src.f[f][(size_t)r * sx + e % nx];
+    }
+}
+
+// Copy the components to the host, in pieces: a thread has one piece packed into
+// pinned memory while it widens the one before to FP64.  A piece is 2 MiB of
+// FP64 at most, one huge page of a large result, whose first touch costs most
+// of the time; up to 8 threads share that.  Measured against one pageable copy
+// and one widening loop per field, read to new arrays: 64^2 112 / 36 us, 200 x
+// 400 247 / 112 us, 128^3 8.0 / 2.1 ms (1 thread 5.9, 4 2.6, 16 4.9 ms),
+// 512 x 256 x 256 236 / 24 ms (1 thread 83, 4 30, 16 21 ms).  A thread takes a
+// million values at least: its start costs 0.1 to 0.5 ms (48^3, 553 thousand
+// values: 0.21 ms on 1 thread, 0.40 ms on 4).
+constexpr size_t kReadThreads = 8, kReadPerThread = size_t(1) << 20;
+template <class AT> int read_back(pulbm_case* c, const ReadBack& rb)
+{
+    const size_t nx = (size_t)c->p.nx, rows = (size_t)c->p.ny * c->p.nz, nc = nx * rows, total = nc * rb.comps;
+    const size_t cap = kPinBytes / sizeof(AT);
+    const int nthreads = (int)std::max<size_t>(
+        1, std::min<size_t>({total / kReadPerThread, kReadThreads, (size_t)std::thread::hardware_concurrency()}));
+    // two pieces to a thread at least (one waits for the link, one is widened)
+    const size_t piece = nthreads == 1 && total <= cap ? std::max<size_t>(total, 1)
+                                                        : std::min(cap, (total + 2 * nthreads - 1) / (2 * nthreads));
+    const size_t npieces = (total + piece - 1) / piece;
+    PackSrc<AT> src = {};
+    for (int f = 0; f < rb.comps; ++f) src.f[f] = (const AT*)rb.dev[f];
+    std::atomic<size_t> next{0};
+    std::atomic<int> err{hipSuccess};
+    int device = 0;
+    HIPC(hipGetDevice(&device));
+    auto work = [&]() -> bool {
+        char* pin[2] = {pin_take(), npieces > 1 ? pin_take() : nullptr};
+        hipEvent_t ev[2] = {nullptr, nullptr};
+        bool ok = pin[0] && (npieces == 1 || pin[1]);
+        hipError_t e = hipSuccess;
+        if (ok && npieces > 1)
+            for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
+        auto pack = [&](size_t n, int k) {
+            const size_t k0 = n * piece, cnt = std::min(piece, total - k0), row = k0 / nx;
+            hipLaunchKernelGGL(k_pack_rows<AT>, dim3((unsigned)std::min<size_t>((cnt + 1023) / 1024, 256)), dim3(256),
+                               0, c->stream, src, (int)(row / rows), (uint32_t)(row % rows), (uint32_t)(k0 % nx),
+                               (uint32_t)rows, (uint32_t)nx, (uint32_t)c->h.sx, (uint32_t)cnt, (AT*)pin[k]);
+            const hipError_t le = hipGetLastError();
+            return le != hipSuccess || npieces == 1 ? le : hipEventRecord(ev[k], c->stream);
+        };
+        size_t at = ok && e == hipSuccess ? next.fetch_add(1) : npieces;
+        int k = 0;
+        if (at < npieces) e = pack(at, 0);
+        while (e == hipSuccess && at < npieces && err.load() == hipSuccess) {
+            const size_t then = next.fetch_add(1);
+            if (then < npieces && (e = pack(then, k ^ 1)) != hipSuccess) break;
+            if ((e = npieces == 1 ? hipStreamSynchronize(c->stream) : hipEventSynchronize(ev[k])) != hipSuccess) break;
+            const AT* v = (const AT*)pin[k];
+            for (size_t i = at * piece, end = std::min(total, i + piece); i < end;) {
+                const size_t o = i % nc, m = std::min(end - i, nc - o);
+                double* dst = rb.host[i / nc] + o;
+                for (size_t j = 0; j < m; ++j) dst[j] = (double)v[j];
+                v += m;
+                i += m;
+            }
+            at = then;
+            k ^= 1;
+        }
+        if (e != hipSuccess) err.store(e);
+        if (err.load() != hipSuccess) (void)hipStreamSynchronize(c->stream);  // pieces in flight
+        for (int j = 0; j < 2; ++j) {
+            if (ev[j]) (void)hipEventDestroy(ev[j]);
+            pin_give(pin[j]);
+        }
+        return ok;
+    };
+    std::thread helper[kReadThreads];
+    int nh = 0;
+    try {
+        while (nh < nthreads - 1) {
+            helper[nh] = std::thread([&] {
+                if (hipSetDevice(device) == hipSuccess) work();
+            });
+            ++nh;
+        }
+    } catch (...) {  // fewer threads: the pieces are shared among those there are
+    }
+    const bool ok = work();
+    for (int k = 0; k < nh; ++k) helper[k].join();
+    if (err.load() != hipSuccess)
+        return fail(PULBM_EDEVICE, "read-back failed: %s", hipGetErrorString((hipError_t)err.load()));
+    if (!ok && next.load() < npieces) return fail(PULBM_ENOMEM, "no pinned memory for the read-back");
+    return PULBM_OK;
+}
+
+}  // namespace
+
 extern "C" int pulbm_read_fields(pulbm_case* c, double* phi, double* P, double* u)
 {
     if (!c) return fail(PULBM_EINVAL, "case is NULL");
     if (!c->ready) return fail(PULBM_ESTATE, "read before init");
     int rc = read_pass(c);
     if (rc) return rc;
-    if ((rc = fetch(c, c->h.phi[c->step & 1], phi, 1))) return rc;
-    if ((rc = fetch(c, c->h.P[(c->step + 1) & 1], P, 1))) return rc;
-    if ((rc = fetch(c, c->h.U[c->step & 1], u, c->p.dim))) return rc;
-    return PULBM_OK;
+    const size_t nc = (size_t)c->p.nx * c->p.ny * c->p.nz, ab = aux_bytes(c->p.store);
+    ReadBack rb;
+    auto field = [&](const void* dev, double* host, int comps) {
+        for (int a = 0; host && a < comps; ++a) {
+            rb.dev[rb.comps] = (const char*)dev + a * (size_t)c->h.N * ab;
+            rb.host[rb.comps++] = host + a * nc;
+        }
+    };
+    field(c->h.phi[c->step & 1], phi, 1);
+    field(c->h.P[(c->step + 1) & 1], P, 1);
+    field(c->h.U[c->step & 1], u, c->p.dim);
+    if (!rb.comps) return PULBM_OK;
+    return ab == 8 ? read_back<double>(c, rb) : read_back<float>(c, rb);
 }
 
 // ============================================= allocation-free read-back
@@ -1029,6 +1202,7 @@ struct pulbm_batch {
     hipStream_t stream = nullptr;  // advances
     hipStream_t side = nullptr;    // admissions and read-backs
     bool own_stream = false;
+    PinUser pins;
     // one device arena of the whole budget; cases are carved from it
     // (first fit, 256-byte granules, neighbouring holes merged on release)
     char* arena = nullptr;
