@@ -458,8 +458,9 @@ void derived_constants(CaseDev& h)
 void launch_case(pulbm_case* c, int off, int which, int parity)
 {
     const int ls = lattice_set(c->p.dim, c->p.q_hydro);
-    if (c->nwide && (which == 1 || which == 2)) launch_wide(ls, c->stream, c->tab, c->h.near_subs + grid_of(c->nwide), off, which);
-    else launch(ls, c->p.store, c->p.collision == 1, c->stream, c->tab, c->hdr, grid_of(c->ntiles), off, which, parity, c->lds);
+    CaseDev* const* alone = (CaseDev* const*)c->d;  // no table (see CaseTab)
+    if (c->nwide && (which == 1 || which == 2)) launch_wide(ls, c->stream, alone, c->h.near_subs + grid_of(c->nwide), off, which);
+    else launch(ls, c->p.store, c->p.collision == 1, c->stream, alone, nullptr, grid_of(c->ntiles), off, which, parity, c->lds);
 }
 
 int upload_desc(pulbm_case* c)
@@ -541,7 +542,7 @@ extern "C" int pulbm_create(const pulbm_params* p, void* dev_arena, size_t arena
     const int ntx = (p->nx + 63) / 64;
     const int tband = std::max(4, std::min(32, std::max(64 / ntx, std::min(16, 128 / ntx))));
     h.map = p->dim == 2 ? tile_map<Model<2>>(*p, tband) : tile_map<Model<3>>(*p, tband);
-    c->ntiles = h.map.ntx * h.map.nty * h.map.ntz;
+    c->ntiles = h.ntiles = h.map.ntx * h.map.nty * h.map.ntz;
     // the wide tiles' rows are twice as high
     if (p->dim == 3) h.wide = tile_map<WideTile>(*p, tband / 2);
     h.delta_theta = p->delta_theta;
