@@ -382,15 +382,16 @@ int collide_lds(const pulbm_params& p, int64_t nodes)
     return p.store == PULBM_STORE_FP32 && p.q_hydro == 27 && pops > (int64_t(320) << 20) ? 12 << 10 : 0;
 }
 
-// Do pressure and velocity take wide tiles?  With 4-byte fields in 3D, from
-// 2048 tiles (512 wide ones, two to a CU) up: measured, pressure + velocity,
-// narrow / wide tiles, 96^3 34.5 / 33.7 us, 128 x 64 x 64 23.9 / 21.9 us,
-// 128^3 45 / 40 us, 512 x 256 x 256 539 / 424 us, but 64^3 16.7 / 19.3 us: too
-// few workgroups, each four times as long.  8-byte fields would leave one
-// workgroup per CU.
-bool wide_tiles(const pulbm_params& p, int ntiles)
+// Do pressure and velocity take wide tiles?  With 4-byte fields in 3D, from 640
+// of them (2.5 to a CU) up: with fewer, each four times as long as a narrow one,
+// the last few decide.  Measured, pressure + velocity, narrow / wide tiles: 576
+// to 600 of them 130 x 60 x 50 dam break 28.0 / 33.5 us, 128 x 70 x 64 24.4 / 24.4,
+// 64 x 100 x 96 25.6 / 25.6; 675 of them 150 x 60 x 60 with a block 31.3 / 28.4, 684
+// 90 x 75 x 70 34.8 / 31.0; 128^3 45 / 40, 512 x 256 x 256 539 / 424 us.  8-byte
+// fields would leave one workgroup per CU.
+bool wide_tiles(const pulbm_params& p, int nwide)
 {
-    return p.dim == 3 && aux_bytes(p.store) == 4 && ntiles >= 2048;
+    return p.dim == 3 && aux_bytes(p.store) == 4 && nwide >= 640;
 }
 
 // The box of wide tiles whose halo reaches the block (the kernels'
@@ -570,8 +571,9 @@ extern "C" int pulbm_create(const pulbm_params* p, void* dev_arena, size_t arena
         h.blk_lo[a] = h.has_block ? p->block_lo[a] : 0;
         h.blk_hi[a] = h.has_block ? p->block_hi[a] : 0;
     }
-    if (wide_tiles(*p, c->ntiles)) {
-        c->nwide = h.wide.ntx * h.wide.nty * h.wide.ntz;
+    const int nwide = h.wide.ntx * h.wide.nty * h.wide.ntz;
+    if (wide_tiles(*p, nwide)) {
+        c->nwide = nwide;
         near_block(h);
     }
     // the collide kernel rebuilds u from a 2-node halo of the new P where
