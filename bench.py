@@ -61,11 +61,12 @@ _CT = {"fp64": "double", "fp32": "float", "fp16": "_Float16", "bf16": "unsigned 
 
 
 def kernel_names(ls, store):
-    """rocprofv3 names of a step's kernels; the collide kernel is one per step
-    parity (even, odd), and a step runs one of them."""
+    """rocprofv3 names of a step's kernels on a large grid; the collide kernel is
+    one per step parity (even, odd), and a step runs one of them."""
     s, a = _CT[store], ("double" if store == "fp64" else "float")
-    return {"moments": f"pulbm::k_moments<{ls}, {s}>", "pressure": f"pulbm::k_pressure<{ls}, {a}>",
-            "velocity": f"pulbm::k_velocity<{ls}, {a}>",
+    w = "_wide" if ls != 2 and store != "fp64" else ""
+    return {"moments": f"pulbm::k_moments<{ls}, {s}>", "pressure": f"pulbm::k_pressure{w}<{ls}, {a}>",
+            "velocity": f"pulbm::k_velocity{w}<{ls}, {a}>",
             "collide": (f"pulbm::k_collide<{ls}, {s}, false, 0>", f"pulbm::k_collide<{ls}, {s}, false, 1>")}
 
 

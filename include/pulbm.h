@@ -118,7 +118,10 @@ int pulbm_step(pulbm_case* c, int64_t nsteps);
 int pulbm_step_timed(pulbm_case* c, int64_t nsteps, double* ms);
 
 /* phi[N], P[N], u[dim*N] of the current state: the moment stage applied to
- * the current distributions without changing them.  Synchronises. */
+ * the current distributions without changing them; each array may be NULL.
+ * Synchronises.  The values pass through pinned pieces of 1 MiB, of which the
+ * library keeps up to 16 while any case or batch lives; from two million values
+ * up to 8 threads of its own share the copy. */
 int pulbm_read_fields(pulbm_case* c, double* phi, double* P, double* u);
 
 /* For callers that cannot allocate (code under HIP graph capture, tight
