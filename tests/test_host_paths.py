@@ -1,0 +1,40 @@
+"""Host side of the library on the CPU, against a stand-in HIP runtime
+(tests/host_paths_driver.c, built here with gcc): what a GPU run cannot show,
+such as pinned memory that runs out or a second device.
+
+- coherent: the host widens a read-back's pieces only where the runtime
+  guarantees that it sees what the GPU wrote (coherent pinned memory, or events
+  that release to the system).
+"""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2512_01027_amd import binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+pytestmark = pytest.mark.skipif(shutil.which("gcc") is None, reason="gcc is not installed")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if not os.path.exists(B.LIB_PATH):
+        pytest.fail("libpulbm.so is not built (run __graft_entry__.build())")
+    exe = str(tmp_path_factory.mktemp("host_paths") / "host_paths")
+    subprocess.run(["gcc", "-std=gnu11", "-O1", "-Wall", "-I", os.path.join(os.path.dirname(HERE), "include"), "-rdynamic",
+                    "-o", exe, os.path.join(HERE, "host_paths_driver.c"), "-ldl"], check=True)
+    return exe
+
+
+def _run(driver, *args):
+    r = subprocess.run([driver, B.LIB_PATH, *map(str, args)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+    return r.stdout
+
+
+@pytest.mark.parametrize("scenario", ["coherent"])
+def test_read_back(driver, scenario):
+    assert _run(driver, scenario).strip().endswith("ok")
