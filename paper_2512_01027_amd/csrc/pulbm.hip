@@ -771,7 +771,8 @@ __global__ __launch_bounds__(256) void k_pack_rows(PackSrc<AT> src, int f0, uint
 // 400 247 / 112 us, 128^3 8.0 / 2.1 ms (1 thread 5.9, 4 2.6, 16 4.9 ms),
 // 512 x 256 x 256 236 / 24 ms (1 thread 83, 4 30, 16 21 ms).  A thread takes a
 // million values at least: its start costs 0.1 to 0.5 ms (48^3, 553 thousand
-// values: 0.21 ms on 1 thread, 0.40 ms on 4).
+// values: 0.21 ms on 1 thread, 0.40 ms on 4).  The case's device is current, in
+// each thread: an event is recorded on streams of its own device only.
 constexpr size_t kReadThreads = 8, kReadPerThread = size_t(1) << 20;
 template <class AT> int read_back(pulbm_case* c, const ReadBack& rb)
 {
@@ -787,8 +788,6 @@ template <class AT> int read_back(pulbm_case* c, const ReadBack& rb)
     for (int f = 0; f < rb.comps; ++f) src.f[f] = (const AT*)rb.dev[f];
     std::atomic<size_t> next{0};
     std::atomic<int> err{hipSuccess};
-    int device = 0;
-    HIPC(hipGetDevice(&device));
     auto work = [&]() -> bool {
         char* pin[2] = {pin_take(), npieces > 1 ? pin_take() : nullptr};
         hipEvent_t ev[2] = {nullptr, nullptr};
@@ -835,7 +834,7 @@ template <class AT> int read_back(pulbm_case* c, const ReadBack& rb)
     try {
         while (nh < nthreads - 1) {
             helper[nh] = std::thread([&] {
-                if (hipSetDevice(device) == hipSuccess) work();
+                if (hipSetDevice(c->device) == hipSuccess) work();
             });
             ++nh;
         }
@@ -855,8 +854,6 @@ extern "C" int pulbm_read_fields(pulbm_case* c, double* phi, double* P, double* 
 {
     if (!c) return fail(PULBM_EINVAL, "case is NULL");
     if (!c->ready) return fail(PULBM_ESTATE, "read before init");
-    int rc = read_pass(c);
-    if (rc) return rc;
     const size_t nc = (size_t)c->p.nx * c->p.ny * c->p.nz, ab = aux_bytes(c->p.store);
     ReadBack rb;
     auto field = [&](const void* dev, double* host, int comps) {
@@ -868,8 +865,13 @@ extern "C" int pulbm_read_fields(pulbm_case* c, double* phi, double* P, double* 
     field(c->h.phi[c->step & 1], phi, 1);
     field(c->h.P[(c->step + 1) & 1], P, 1);
     field(c->h.U[c->step & 1], u, c->p.dim);
-    if (!rb.comps) return PULBM_OK;
-    return ab == 8 ? read_back<double>(c, rb) : read_back<float>(c, rb);
+    int cur = 0;
+    HIPC(hipGetDevice(&cur));
+    if (cur != c->device) HIPC(hipSetDevice(c->device));
+    int rc = read_pass(c);
+    if (!rc && rb.comps) rc = ab == 8 ? read_back<double>(c, rb) : read_back<float>(c, rb);
+    if (cur != c->device) (void)hipSetDevice(cur);
+    return rc;
 }
 
 // ============================================= allocation-free read-back

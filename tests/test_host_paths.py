@@ -5,6 +5,7 @@ such as pinned memory that runs out or a second device.
 - coherent: the host widens a read-back's pieces only where the runtime
   guarantees that it sees what the GPU wrote (coherent pinned memory, or events
   that release to the system).
+- device: a case is read from a thread whose current device is another one.
 """
 import os
 import shutil
@@ -35,6 +36,6 @@ def _run(driver, *args):
     return r.stdout
 
 
-@pytest.mark.parametrize("scenario", ["coherent"])
+@pytest.mark.parametrize("scenario", ["coherent", "device"])
 def test_read_back(driver, scenario):
     assert _run(driver, scenario).strip().endswith("ok")
