@@ -37,7 +37,7 @@ extern "C" {
 
 #define PULBM_OK 0
 #define PULBM_EINVAL (-1)    /* bad argument or parameter                         */
-#define PULBM_ENOMEM (-2)    /* device allocation failed / arena too small        */
+#define PULBM_ENOMEM (-2)    /* allocation failed / arena too small               */
 #define PULBM_EDEVICE (-3)   /* a HIP call failed                                 */
 #define PULBM_EDIVERGED (-4) /* non-finite values found in the fields             */
 #define PULBM_ESTATE (-5)    /* call out of order (e.g. step before init)         */
@@ -120,8 +120,9 @@ int pulbm_step_timed(pulbm_case* c, int64_t nsteps, double* ms);
 /* phi[N], P[N], u[dim*N] of the current state: the moment stage applied to
  * the current distributions without changing them; each array may be NULL.
  * Synchronises.  The values pass through pinned pieces of 1 MiB, of which the
- * library keeps up to 16 while any case or batch lives; from two million values
- * up to 8 threads of its own share the copy. */
+ * library keeps up to 16 while any case or batch lives, or through pageable
+ * memory if no pinned pieces are to be had; from two million values up to 8
+ * threads of its own share the copy. */
 int pulbm_read_fields(pulbm_case* c, double* phi, double* P, double* u);
 
 /* For callers that cannot allocate (code under HIP graph capture, tight

@@ -763,6 +763,26 @@ __global__ __launch_bounds__(256) void k_pack_rows(PackSrc<AT> src, int f0, uint
     }
 }
 
+// The components one by one through pageable memory, where no pinned pieces are
+// to be had.
+template <class AT> int read_back_pageable(pulbm_case* c, const ReadBack& rb)
+{
+    const size_t nx = (size_t)c->p.nx, sx = (size_t)c->h.sx, rows = (size_t)c->p.ny * c->p.nz;
+    std::vector<AT> raw;
+    try {
+        raw.resize(rows * sx);
+    } catch (...) {
+        return fail(PULBM_ENOMEM, "no host memory for the read-back");
+    }
+    for (int f = 0; f < rb.comps; ++f) {
+        HIPC(hipMemcpyAsync(raw.data(), rb.dev[f], raw.size() * sizeof(AT), hipMemcpyDeviceToHost, c->stream));
+        HIPC(hipStreamSynchronize(c->stream));
+        for (size_t r = 0; r < rows; ++r)
+            for (size_t i = 0; i < nx; ++i) rb.host[f][r * nx + i] = (double)raw[r * sx + i];
+    }
+    return PULBM_OK;
+}
+
 // Copy the components to the host, in pieces: a thread has one piece packed into
 // pinned memory while it widens the one before to FP64.  A piece is 2 MiB of
 // FP64 at most, one huge page of a large result, whose first touch costs most
@@ -844,8 +864,7 @@ template <class AT> int read_back(pulbm_case* c, const ReadBack& rb)
     for (int k = 0; k < nh; ++k) helper[k].join();
     if (err.load() != hipSuccess)
         return fail(PULBM_EDEVICE, "read-back failed: %s", hipGetErrorString((hipError_t)err.load()));
-    if (!ok && next.load() < npieces) return fail(PULBM_ENOMEM, "no pinned memory for the read-back");
-    return PULBM_OK;
+    return !ok && next.load() < npieces ? read_back_pageable<AT>(c, rb) : PULBM_OK;
 }
 
 }  // namespace

@@ -6,6 +6,7 @@ such as pinned memory that runs out or a second device.
   guarantees that it sees what the GPU wrote (coherent pinned memory, or events
   that release to the system).
 - device: a case is read from a thread whose current device is another one.
+- nopinned, onepinned: no pinned memory, or one piece of it, is to be had.
 """
 import os
 import shutil
@@ -36,6 +37,6 @@ def _run(driver, *args):
     return r.stdout
 
 
-@pytest.mark.parametrize("scenario", ["coherent", "device"])
+@pytest.mark.parametrize("scenario", ["coherent", "device", "nopinned", "onepinned"])
 def test_read_back(driver, scenario):
     assert _run(driver, scenario).strip().endswith("ok")
