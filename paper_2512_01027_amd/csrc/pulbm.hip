@@ -210,21 +210,32 @@ struct {
     int n = 0, users = 0;
 } g_pins;
 
+// Pinned memory is had and given back while another stream of the caller's may
+// be under capture, when the runtime refuses both in any but the relaxed mode.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+void pin_free(char* p)
+{
+    RelaxedCapture relaxed;
+    (void)hipHostFree(p);
+}
+
 char* pin_take()
 {
     {
         std::lock_guard<std::mutex> hold(g_pins.lock);
         if (g_pins.n) return g_pins.idle[--g_pins.n];
     }
-    // (another stream of the caller's may be under capture)
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    RelaxedCapture relaxed;
     char* p = nullptr;
     if (hipHostMalloc((void**)&p, kPinBytes, hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
         p = nullptr;
         (void)hipGetLastError();
     }
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
     return p;
 }
 
@@ -238,7 +249,7 @@ void pin_give(char* p)
             return;
         }
     }
-    (void)hipHostFree(p);
+    pin_free(p);
 }
 
 // Held by every case and batch.
@@ -257,7 +268,7 @@ struct PinUser {
             if (--g_pins.users == 0)
                 while (g_pins.n) gone[n++] = g_pins.idle[--g_pins.n];
         }
-        while (n) (void)hipHostFree(gone[--n]);
+        while (n) pin_free(gone[--n]);
     }
     PinUser(const PinUser&) = delete;
     PinUser& operator=(const PinUser&) = delete;

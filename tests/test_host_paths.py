@@ -7,6 +7,7 @@ such as pinned memory that runs out or a second device.
   that release to the system).
 - device: a case is read from a thread whose current device is another one.
 - nopinned, onepinned: no pinned memory, or one piece of it, is to be had.
+- capture: the last case goes while a stream is under capture in global mode.
 """
 import os
 import shutil
@@ -37,6 +38,6 @@ def _run(driver, *args):
     return r.stdout
 
 
-@pytest.mark.parametrize("scenario", ["coherent", "device", "nopinned", "onepinned"])
+@pytest.mark.parametrize("scenario", ["coherent", "device", "nopinned", "onepinned", "capture"])
 def test_read_back(driver, scenario):
     assert _run(driver, scenario).strip().endswith("ok")
