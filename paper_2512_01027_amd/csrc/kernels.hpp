@@ -1888,6 +1888,20 @@ template <class S> struct Flow2D {
     CT P[Halo2<Model<2>, 2>::R::N];
 };
 
+// LDS bytes that a 2D collide's launch asks for: h (parked there but in 2-byte
+// storage), in the same place as the fields of the rebuild if some case of the
+// launch is FUSED, which are read for the last time before h is parked.  In FP64
+// a CU's LDS then holds 3 workgroups with a fused case and 5 without; with room
+// for both in every launch it held 2 (step, before / after: 1024^2 104 / 96 us,
+// with walls 109 / 99, with a block 118 / 111; serving 12 of 200 x 400 with walls
+// 137 / 120, with a block each 143 / 128; a batch that mixes both kinds 153 /
+// 139).  The other storage widths held 5 and more: the same within 2%.
+template <class S> constexpr int collide_lds_2d(bool fused)
+{
+    const int h = sizeof(S) == 2 ? 0 : (int)sizeof(S) * D2Q9::Q * 256;
+    return fused && (int)sizeof(Flow2D<S>) > h ? (int)sizeof(Flow2D<S>) : h;
+}
+
 // The node that a 2D cell beyond a wall or the open end mirrors: (x - dx, y - dy).
 struct Mirror {
     int dx, dy;
@@ -2366,23 +2380,31 @@ __global__ __launch_bounds__(256) PULBM_COLLIDE_ATTR void k_collide(CaseTab case
     using CT = typename Codec<S>::CT;
     using R = typename Halo1<Mo, DIMV>::R;
     __shared__ TileCells<LS, S> sC;
-    __shared__ S sH[sizeof(S) == 2 ? 1 : H::Q][256];
     // the new P two nodes deep, for cases whose collide rebuilds u
     __shared__ CT sP2[can_fuse_u<LS, S>() ? Halo2<Mo, DIMV>::R::N : 1];
-    // P*, u* and the new P of a 2D tile, for cases whose collide rebuilds both
-    struct None {};
-    __shared__ std::conditional_t<LS == 2, Flow2D<S>, None> s2;
+    S(*sH)[256];
+    Flow2D<S>* s2 = nullptr;
+    if constexpr (LS == 2) {
+        // h, and before it P*, u* and the new P for cases whose collide rebuilds
+        // both, in the LDS of the launch (collide_lds_2d)
+        extern __shared__ __align__(16) char collide_dyn[];
+        sH = (S(*)[256])collide_dyn;
+        s2 = (Flow2D<S>*)collide_dyn;
+    } else {
+        __shared__ S sHs[sizeof(S) == 2 ? 1 : H::Q][256];
+        sH = sHs;
+    }
     const TileCtx t = tile_ctx<Mo>(cases, hdr, step_off);
     if (!t.active || (int)(t.step & 1) != PAR) return;
     CDesc& cs = *t.cs;
     if (tile_at_wall<Mo>(cs, t.ox, t.oy, t.oz)) {
-        collide_tile<LS, S, true, BGK, R, PAR>(cs, t, sC, sH, sP2, (Flow2D<S>*)&s2);
+        collide_tile<LS, S, true, BGK, R, PAR>(cs, t, sC, sH, sP2, s2);
     } else if (PAR == 1 && t.ox >= 1 && t.ox + Mo::TX < cs.nx && t.oy >= 1 && t.oy + Mo::TY < cs.ny &&
                (DIMV == 2 || (t.oz >= 1 && t.oz + Mo::TZ < cs.nz))) {
         // every node of the tile has its neighbours inside the grid
-        collide_tile<LS, S, false, BGK, R, 2>(cs, t, sC, sH, sP2, (Flow2D<S>*)&s2);
+        collide_tile<LS, S, false, BGK, R, 2>(cs, t, sC, sH, sP2, s2);
     } else {
-        collide_tile<LS, S, false, BGK, R, PAR>(cs, t, sC, sH, sP2, (Flow2D<S>*)&s2);
+        collide_tile<LS, S, false, BGK, R, PAR>(cs, t, sC, sH, sP2, s2);
     }
 }
 

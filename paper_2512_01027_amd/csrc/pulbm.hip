@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -352,8 +353,8 @@ void launch_dim(int store, hipStream_t st, CaseDev* const* tab, const int* hdr, 
 // parity: the step parity of every case of the table for this launch (its
 // device step counter plus off), 0 or 1, when the host knows it (a single
 // case); -1 when cases may differ (serving batches): then the collide
-// kernels of both parities are launched.  lds: LDS bytes the collide's
-// workgroups are given beyond their own (collide_lds).
+// kernels of both parities are launched.  lds: LDS bytes that the collide's
+// launch asks for (collide_lds).
 void launch(int ls, int store, bool bgk, hipStream_t st, CaseDev* const* tab, const int* hdr, int blocks, int off,
             int which, int parity = -1, int lds = 0)
 {
@@ -383,16 +384,24 @@ void launch_init(int ls, int store, hipStream_t st, CaseDev* const* tab, const i
 #undef PULBM_INIT_CASE
 }
 
-// LDS bytes added to the collide's workgroups to hold them to 3 per CU instead
-// of 4.  4-byte D3Q27 populations past the 256 MB last-level cache are bound by
-// HBM, and a fourth workgroup only widens the set of halo rows that compete
-// for the L2 (measured with 3 / 4 per CU, step: 256^3 bubble 2.00 / 2.08 ms,
-// 128^3 droplet, 386 MB of populations, 244 / 249 us, 100^3 bubble 180 / 183
-// us); smaller grids are bound by latency and take 4 (90x75x70 BGK droplet
-// 102 / 94 us, 128x110x110 dam break 208 / 204 us).  D3Q19 hydro is held to 3
-// by the u rebuild's halo; the other storage widths gain from every workgroup.
-int collide_lds(const pulbm_params& p, int64_t nodes)
+// LDS bytes that the launch of a case's collide asks for.  2D: collide_lds_2d.
+// 3D: what holds the workgroups to 3 per CU instead of 4.  4-byte D3Q27
+// populations past the 256 MB last-level cache are bound by HBM, and a fourth
+// workgroup only widens the set of halo rows that compete for the L2 (measured
+// with 3 / 4 per CU, step: 256^3 bubble 2.00 / 2.08 ms, 128^3 droplet, 386 MB of
+// populations, 244 / 249 us, 100^3 bubble 180 / 183 us); smaller grids are bound
+// by latency and take 4 (90x75x70 BGK droplet 102 / 94 us, 128x110x110 dam break
+// 208 / 204 us).  D3Q19 hydro is held to 3 by the u rebuild's halo; the other
+// storage widths gain from every workgroup.
+int collide_lds(const pulbm_params& p, int64_t nodes, int fuse_u)
 {
+    if (p.dim == 2) {
+        switch (p.store) {
+            case PULBM_STORE_FP64: return collide_lds_2d<double>(fuse_u == 2);
+            case PULBM_STORE_FP32: return collide_lds_2d<float>(fuse_u == 2);
+            default: return collide_lds_2d<uint16_t>(fuse_u == 2);
+        }
+    }
     const int64_t pops = (int64_t)(p.q_phase + p.q_hydro) * nodes * store_bytes(p.store);
     return p.store == PULBM_STORE_FP32 && p.q_hydro == 27 && pops > (int64_t(320) << 20) ? 12 << 10 : 0;
 }
@@ -602,13 +611,14 @@ extern "C" int pulbm_create(const pulbm_params* p, void* dev_arena, size_t arena
     // in 2D it rebuilds P and u (rebuild_2d), where one +-n wraps three nodes
     // past either end of both axes.  Measured against the separate kernels, step:
     // 64^2 FP64 13.8 / 11.4 us, 200 x 400 with walls FP32 19.4 / 15.4 us, 300^2
-    // FP16 17.4 / 11.7 us, 1024^2 FP16 55 / 45 us, 1000 x 600 FP64 78 / 74 us:
-    // every size gains, the small ones two launches, the large ones the fields
-    // that no longer pass through memory.
+    // FP16 17.4 / 11.7 us, 1024^2 FP16 55 / 45 us, FP64 106 / 95 us, 8192 x 4096 FP64
+    // 3.81 / 3.37 ms, 8192^2 FP32 3.81 / 3.26 ms, FP16 2.54 / 2.23 ms: every size
+    // gains, the small ones two launches, the large ones the fields that no
+    // longer pass through memory.
     if (p->dim == 2 && !h.has_block && p->nx >= 3 && p->ny >= 3) h.fuse_u = 2;
     codec_constants(*p, h);
     derived_constants(h);
-    c->lds = collide_lds(*p, h.N);
+    c->lds = collide_lds(*p, h.N, h.fuse_u);
     c->d = (CaseDev*)(c->base + L.desc);
     c->tab = (CaseDev**)(c->base + L.tab);
     c->hdr = (int*)(c->base + L.tab + sizeof(CaseDev*));
@@ -1275,8 +1285,9 @@ struct pulbm_batch {
         int which = 0;
         int cap = 0, ncases = 0, tiles = 0, grid = 0;
         int kernels = 0;  // bit w: some case's step runs kernel w
-        // by 64 ksteps + 16 parity (0, 1; 2 mixed) + kernels, captured for `grid` blocks
-        std::map<int, hipGraphExec_t> graphs;
+        int lds = 0;      // the collide's launch (2D: the most a case asks for)
+        // by ksteps, parity (-1 mixed), kernels and lds, captured for `grid` blocks
+        std::map<std::array<int, 4>, hipGraphExec_t> graphs;
     } tab[6];  // index (lattice set - 2) + 3 * collision
     bool dirty = true;
 };
@@ -1382,11 +1393,12 @@ int rebuild_tables(pulbm_batch* b)
         int* hdr = (int*)(t.stage[t.which] + t.cap * sizeof(CaseDev*));
         int n = 0;
         hdr[2] = 0;
-        t.kernels = 0;
+        t.kernels = t.lds = 0;
         for (auto& s : b->slots)
             if (s.c && lattice_set(s.c->p.dim, s.c->p.q_hydro) == ls && s.c->p.collision == coll) {
                 ptr[n] = s.c->d;
                 for (int w = 0; w < kStepKernels; ++w) t.kernels |= step_runs(s.c->h.fuse_u, w) ? 1 << w : 0;
+                if (ls == 2) t.lds = std::max(t.lds, s.c->lds);
                 hdr[3 + n] = hdr[2 + n] + s.c->ntiles;
                 ++n;
             }
@@ -1518,7 +1530,7 @@ extern "C" int pulbm_batch_advance(pulbm_batch* b, int32_t ksteps)
                 par = par == -2 ? p : (par == p ? p : -1);
             }
         if (par == -2) par = 0;
-        const int key = ksteps * 64 + (par < 0 ? 2 : par) * 16 + t.kernels;
+        const std::array<int, 4> key = {ksteps, par, t.kernels, t.lds};
         auto it = t.graphs.find(key);
         if (it == t.graphs.end()) {
             hipGraph_t g = nullptr;
@@ -1528,7 +1540,7 @@ extern "C" int pulbm_batch_advance(pulbm_batch* b, int32_t ksteps)
                 for (int w = 0; w < kStepKernels; ++w)
                     if (t.kernels & 1 << w)
                         launch(di % 3 + 2, b->store, di / 3 == 1, b->stream, t.dtab, t.dhdr, t.grid, k, w,
-                               par < 0 ? -1 : (par + k) & 1);
+                               par < 0 ? -1 : (par + k) & 1, t.lds);
             hipLaunchKernelGGL(k_advance, dim3((t.cap + 63) / 64), dim3(64), 0, b->stream, t.dtab, t.dhdr, ksteps);
             HIPC(hipStreamEndCapture(b->stream, &g));
             HIPC(hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));

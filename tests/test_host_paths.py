@@ -41,3 +41,17 @@ def _run(driver, *args):
 @pytest.mark.parametrize("scenario", ["coherent", "device", "nopinned", "onepinned", "capture"])
 def test_read_back(driver, scenario):
     assert _run(driver, scenario).strip().endswith("ok")
+
+
+@pytest.mark.parametrize("store", [0, 1, 2, 3])
+def test_2d_collide_lds(driver, store):
+    """LDS that the 2D collide's launch asks for: the rebuild's fields (P*, u* and
+    phi of 700 cells, 544 of P) only where the case's collide rebuilds P and u, not
+    for a case with a block; no more than the larger of them and h."""
+    sb, ab = [8, 4, 2, 2][store], 8 if store == 0 else 4
+    h = 0 if sb == 2 else 9 * 256 * sb
+    case = lambda block: [int(v) for v in _run(driver, "lds", "k_collide", 2, 64, 40, 1, store, 0, block, 2).split()]  # noqa: E731
+    assert case(1) == [h, h]
+    fused = case(0)
+    assert fused == fused[:1] * 2
+    assert max(h, (5 * 700 + 544) * ab) <= fused[0] < max(h, (5 * 700 + 544) * ab) + 64
