@@ -2188,15 +2188,18 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCe
         }
     }
     if constexpr (LS == 2) {
-        // the new P and u of the tile's own nodes
+        // the new P of the tile's own nodes, and in 2-byte storage their u, the
+        // codec's reference of the next step (no kernel reads u otherwise)
         if (fused2d && inside) {
-            CT f[F::NF];
-            const int c = R::idx(lx + 1, ly + 1, 0);
-            sC.get({c * 16, c * (int)sizeof(CT)}, 0, f);
             *at_node<CT>(cs.P[(t.step + 1) & 1], n) = Pnew;
-            const Slots<CT> Un = slots<CT>(cs.U[t.step & 1], cs.N);
+            if constexpr (sizeof(S) == 2) {
+                CT f[F::NF];
+                const int c = R::idx(lx + 1, ly + 1, 0);
+                sC.get({c * 16, c * (int)sizeof(CT)}, 0, f);
+                const Slots<CT> Un = slots<CT>(cs.U[t.step & 1], cs.N);
 #pragma unroll
-            for (int a = 0; a < DIMV; ++a) *Un.at(a, n * (uint32_t)sizeof(CT)) = f[F::U + a];
+                for (int a = 0; a < DIMV; ++a) *Un.at(a, n * (uint32_t)sizeof(CT)) = f[F::U + a];
+            }
         }
     }
     if (!inside) return;
