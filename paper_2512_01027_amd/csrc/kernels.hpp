@@ -2056,7 +2056,15 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCe
     const int x = t.ox + lx, y = t.oy + ly, z = t.oz + lz;
     // block nodes carry no fluid and are skipped like nodes past the grid
     const bool inside = x < cs.nx && y < cs.ny && z < cs.nz && !(WALL && in_block(cs, x, y, z));
-    const uint32_t n = inside ? (uint32_t)x + (uint32_t)cs.sx * ((uint32_t)y + (uint32_t)cs.ny * (uint32_t)z) : 0u;
+    // What a lane outside the grid loads is never used.  It loads the nearest
+    // node, in a line that a lane inside loads (all of them node 0 made its lines
+    // a hot spot of the whole chip, 100 x 90 x 80, FP32 odd collide 72 / 58 us,
+    // FP16 48 / 41), or nothing in a tile at a wall, where the nearest node's
+    // registers cost more than the branch (512 x 256 x 256 dam break, FP16 odd
+    // collide 1.55 / 1.48 ms).
+    const int xc = WALL ? (inside ? x : 0) : min(x, cs.nx - 1), yc = WALL ? (inside ? y : 0) : min(y, cs.ny - 1),
+              zc = WALL ? (inside ? z : 0) : min(z, cs.nz - 1);
+    const uint32_t n = (uint32_t)xc + (uint32_t)cs.sx * ((uint32_t)yc + (uint32_t)cs.ny * (uint32_t)zc);
     const uint32_t nb = n * (uint32_t)sizeof(S), na = n * (uint32_t)(sizeof(S) == 2 ? 4 : sizeof(CT));
     // the step's parity, which decides the slots the AA pattern reads and
     // writes.  PAR 0: even, fixed at compile time.  PAR 1: odd, read again at
@@ -2067,7 +2075,7 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCe
     // whose offsets are then the strides (scalars).
     const bool odd = PAR == 0 ? false : (PAR == 2 ? true : (bool)(step_parity(cs, t) & 1));
     const Nav nv = PAR == 2 ? make_nav_inner(cs, (int)sizeof(S))
-                            : make_nav(cs, inside ? x : 0, inside ? y : 0, inside ? z : 0, (int)sizeof(S));
+                            : make_nav(cs, xc, yc, zc, (int)sizeof(S));
     // stores stream past L2 on even steps (FP32 even collide 3% faster); on
     // odd steps, shifted by one node in x, each line is written partly by
     // this tile and partly by its x neighbour, and kept in L2 the parts merge
@@ -2083,7 +2091,7 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCe
     CT php = 0;  // reference of the incoming h (2-byte storage)
     CT dP = 0;   // BGK: (previous P - new P) / (rho_ref T), restores the stored rest population
     CT ur[3] = {0, 0, 0};  // BGK, 2-byte storage: reference of the incoming g
-    {
+    if (!WALL || inside) {
         php = h_reference<S>(cs.phi[(t.step + 1) & 1], n);
         if constexpr (BGK) u_reference<S, DIMV>(cs.U[(t.step + 1) & 1], cs.N, n, ur);
 #pragma unroll
