@@ -385,25 +385,34 @@ void launch_init(int ls, int store, hipStream_t st, CaseDev* const* tab, const i
 }
 
 // LDS bytes that the launch of a case's collide asks for.  2D: collide_lds_2d.
-// 3D: what holds the workgroups to 3 per CU instead of 4.  4-byte D3Q27
-// populations past the 256 MB last-level cache are bound by HBM, and a fourth
-// workgroup only widens the set of halo rows that compete for the L2 (measured
-// with 3 / 4 per CU, step: 256^3 bubble 2.00 / 2.08 ms, 128^3 droplet, 386 MB of
-// populations, 244 / 249 us, 100^3 bubble 180 / 183 us); smaller grids are bound
-// by latency and take 4 (90x75x70 BGK droplet 102 / 94 us, 128x110x110 dam break
-// 208 / 204 us).  D3Q19 hydro is held to 3 by the u rebuild's halo; the other
-// storage widths gain from every workgroup.
+// 3D: what holds the workgroups to 3 per CU instead of 4, where a fourth only
+// widens the set of halo rows that compete for the L2: the filter collision of
+// 4-byte D3Q27 populations too large for the 256 MB last-level cache, with the
+// fields beside them from about 128 MiB of populations (measured, step with 4 / 3
+// per CU, MiB: 64^3 bubble, 46, 38 / 39 us; 80^3, 108, 90.5 / 90.1; 96^3, 155, 126 /
+// 124; 128 x 120 x 120, 323, 250 / 245; 128^3, 368, 244 / 238; 160 x 128 x 100, 359,
+// 261 / 261; 192^3, 1242, 838 / 845; 256 x 192 x 192, 1656, 1183 / 1139).  Tiles at
+// walls, whose slots are chosen at run time, are bound by latency, and their
+// share decides up to 512 MiB (with walls on all faces: 96^3 137 / 142; 128^3 251 /
+// 257; 256 x 96 x 96, 414, 305 / 307; 150^3, 632, 525 / 522; 192^3 886 / 873; 256 x 192
+// x 192 1193 / 1149).  BGK is bound by its instructions at every size (128^3 276 /
+// 299, 512 x 256 x 256 4595 / 4915).  D3Q19 hydro is held to 3 by the u rebuild's
+// halo; the other storage widths gain from every workgroup.
+int collide_lds_3d(const pulbm_params& p, int64_t pops, bool walls)
+{
+    const bool held = p.store == PULBM_STORE_FP32 && p.q_hydro == 27 && p.collision == 0;
+    return held && pops > (int64_t(walls ? 512 : 128) << 20) ? 12 << 10 : 0;
+}
+int64_t pop_bytes(const pulbm_params& p, int64_t nodes) { return (int64_t)(p.q_phase + p.q_hydro) * nodes * store_bytes(p.store); }
+bool any_wall(const pulbm_params& p) { return p.wall[0] || p.wall[1] || p.wall[2]; }
 int collide_lds(const pulbm_params& p, int64_t nodes, int fuse_u)
 {
-    if (p.dim == 2) {
-        switch (p.store) {
-            case PULBM_STORE_FP64: return collide_lds_2d<double>(fuse_u == 2);
-            case PULBM_STORE_FP32: return collide_lds_2d<float>(fuse_u == 2);
-            default: return collide_lds_2d<uint16_t>(fuse_u == 2);
-        }
+    if (p.dim == 3) return collide_lds_3d(p, pop_bytes(p, nodes), any_wall(p));
+    switch (p.store) {
+        case PULBM_STORE_FP64: return collide_lds_2d<double>(fuse_u == 2);
+        case PULBM_STORE_FP32: return collide_lds_2d<float>(fuse_u == 2);
+        default: return collide_lds_2d<uint16_t>(fuse_u == 2);
     }
-    const int64_t pops = (int64_t)(p.q_phase + p.q_hydro) * nodes * store_bytes(p.store);
-    return p.store == PULBM_STORE_FP32 && p.q_hydro == 27 && pops > (int64_t(320) << 20) ? 12 << 10 : 0;
 }
 
 // Do pressure and velocity take wide tiles?  With 4-byte fields in 3D, from 640
@@ -1285,7 +1294,7 @@ struct pulbm_batch {
         int which = 0;
         int cap = 0, ncases = 0, tiles = 0, grid = 0;
         int kernels = 0;  // bit w: some case's step runs kernel w
-        int lds = 0;      // the collide's launch (2D: the most a case asks for)
+        int lds = 0;      // the collide's launch: 2D the most a case asks for, 3D by all populations
         // by ksteps, parity (-1 mixed), kernels and lds, captured for `grid` blocks
         std::map<std::array<int, 4>, hipGraphExec_t> graphs;
     } tab[6];  // index (lattice set - 2) + 3 * collision
@@ -1394,11 +1403,15 @@ int rebuild_tables(pulbm_batch* b)
         int n = 0;
         hdr[2] = 0;
         t.kernels = t.lds = 0;
+        int64_t pops = 0;
+        bool walls = false;
         for (auto& s : b->slots)
             if (s.c && lattice_set(s.c->p.dim, s.c->p.q_hydro) == ls && s.c->p.collision == coll) {
                 ptr[n] = s.c->d;
                 for (int w = 0; w < kStepKernels; ++w) t.kernels |= step_runs(s.c->h.fuse_u, w) ? 1 << w : 0;
-                if (ls == 2) t.lds = std::max(t.lds, s.c->lds);
+                pops += pop_bytes(s.c->p, s.c->h.N);
+                walls = walls || any_wall(s.c->p);
+                t.lds = ls == 2 ? std::max(t.lds, s.c->lds) : collide_lds_3d(s.c->p, pops, walls);
                 hdr[3 + n] = hdr[2 + n] + s.c->ntiles;
                 ++n;
             }

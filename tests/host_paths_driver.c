@@ -274,11 +274,12 @@ int main(int argc, char** argv)
     /* one piece, several pieces on one thread, several threads; padded rows */
     const pulbm_params sizes[3] = {params(2, 37, 29, 1, PULBM_STORE_FP64), params(3, 61, 47, 33, PULBM_STORE_FP32),
                                    params(3, 131, 83, 51, PULBM_STORE_FP16)};
-    if (!strcmp(s, "lds")) {  /* <kernel> <dim> <nx> <ny> <nz> <store> <wall> <block> <steps> */
+    if (!strcmp(s, "lds")) {  /* <kernel> <dim> <nx> <ny> <nz> <store> <wall> <block> <steps> [<collision>] */
         pulbm_params p = params(atoi(argv[4]), atoi(argv[5]), atoi(argv[6]), atoi(argv[7]), atoi(argv[8]));
         for (int a = 0; a < p.dim; ++a) p.wall[a] = atoi(argv[9]);
         if (atoi(argv[10]))
             for (int a = 0; a < 3; ++a) p.block_lo[a] = a < p.dim ? 2 : 0, p.block_hi[a] = a < p.dim ? 5 : 1;
+        p.collision = argc > 12 ? atoi(argv[12]) : 0;
         size_t bytes = 0;
         pulbm_case* c = NULL;
         if (required(&p, &bytes)) fail("required_bytes");

@@ -55,3 +55,15 @@ def test_2d_collide_lds(driver, store):
     fused = case(0)
     assert fused == fused[:1] * 2
     assert max(h, (5 * 700 + 544) * ab) <= fused[0] < max(h, (5 * 700 + 544) * ab) + 64
+
+
+@pytest.mark.parametrize("store,bgk,wall,n,held", [
+    (1, 0, 0, (64, 64, 64), False), (1, 0, 0, (100, 100, 100), True), (1, 0, 1, (100, 100, 100), False),
+    (1, 0, 1, (128, 128, 128), False), (1, 0, 1, (192, 128, 128), True), (1, 1, 0, (128, 128, 128), False),
+    (2, 0, 0, (192, 128, 128), False)])
+def test_3d_collide_lds(driver, store, bgk, wall, n, held):
+    """4 workgroups of the 4-byte D3Q27 collide to a CU (40,576 bytes each of its
+    160 KiB), or 3 where its launch asks for 12 KiB more: the filter collision's
+    from 128 MiB of populations, 512 MiB with walls."""
+    lds = _run(driver, "lds", "k_collide", 3, *n, store, wall, 0, 2, bgk).split()
+    assert [int(v) for v in lds] == [12288 if held else 0] * 2
