@@ -296,9 +296,9 @@ template <class Mo> __device__ __forceinline__ TileCtx wide_ctx(CaseTab cases, i
 // buffer resource (SGPRs) and each lane supplies only its 32-bit byte offset.
 // Through plain pointers the compiler forms every population address as a
 // per-lane 64-bit sum; through buffer resources the collision kernel issues
-// about 12% fewer vector instructions and keeps fewer registers live.  An
-// offset past the slot would read 0 and write nothing (none is formed: every
-// target node lies in the grid).  aux 2 marks the access non-temporal.
+// about 12% fewer vector instructions and keeps fewer registers live.  No
+// offset past the slot is formed: every target node lies in the grid.  aux 2
+// marks the access non-temporal.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(PULBM_GLB char* base, uint32_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000);
@@ -323,7 +323,16 @@ template <bool NT, class T> __device__ __forceinline__ void buf_st(__amdgpu_buff
     }
 }
 
-template <class T>
+// PAIRED: one resource serves the two slots of an opposite pair (2 slot_bytes
+// stay below 2^32), the second at a scalar offset; otherwise a slot has its
+// own.  A resource takes four SGPRs, and the collide, which loads and stores
+// every slot, spills twice as many with one per slot (160^3 walls, FP32 odd
+// collide 281 paired / 298 us).  The moments only load: one per slot in 4-byte 3D
+// storage (128^3 odd 101.9 paired / 100.1 us), paired in the others (512 x 256 x
+// 256 BF16 odd 864 / 941 us, 2000 x 1200 FP64 step 297 / 310; FP16 the same within
+// 0.5% of the step; 2D FP32, where forming them is not hidden on small grids, a
+// batch of 12 of 128^2 13.0 / 13.4, though 1024^2 54.4 / 52.8).
+template <class T, bool PAIRED = true>
 struct Slots {
     PULBM_GLB char* base;
     uint64_t slot_bytes;  // N * sizeof(T), below 2^31
@@ -331,20 +340,17 @@ struct Slots {
     {
         return (PULBM_GLB T*)(base + (uint64_t)slot * slot_bytes + boff);
     }
-    // One resource serves the two slots of an opposite pair (2 slot_bytes stay
-    // below 2^32), the second at a scalar offset: a resource takes four SGPRs,
-    // and one per slot kept more of them live than there are.
-    __device__ static __forceinline__ int pair(int slot) { return slot == 0 ? 0 : ((slot - 1) | 1); }
+    __device__ static __forceinline__ int first(int slot) { return !PAIRED || slot == 0 ? slot : ((slot - 1) | 1); }
     __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(int slot) const
     {
-        return buf_rsrc(base + (uint64_t)pair(slot) * slot_bytes, 2u * (uint32_t)slot_bytes);
+        return buf_rsrc(base + (uint64_t)first(slot) * slot_bytes, (PAIRED ? 2u : 1u) * (uint32_t)slot_bytes);
     }
-    __device__ __forceinline__ uint32_t soff(int slot) const { return slot == pair(slot) ? 0u : (uint32_t)slot_bytes; }
+    __device__ __forceinline__ uint32_t soff(int slot) const { return slot == first(slot) ? 0u : (uint32_t)slot_bytes; }
 };
 
-template <class T> __device__ __forceinline__ Slots<T> slots(void* p, int64_t N)
+template <class T, bool PAIRED = true> __device__ __forceinline__ Slots<T, PAIRED> slots(void* p, int64_t N)
 {
-    Slots<T> s;
+    Slots<T, PAIRED> s;
     s.base = (PULBM_GLB char*)p;
     s.slot_bytes = (uint64_t)N * sizeof(T);
     return s;
@@ -505,8 +511,8 @@ constexpr int kNtWide = kLoadMomentsEven | kLoadCollide | kStoreCollide, kNtHalf
 template <class S, int A> constexpr bool nt_access() { return ((sizeof(S) >= 4 ? kNtWide : kNtHalf) & A) != 0; }
 
 // Population arriving at the node (byte offset nb) along direction i.
-template <class L, bool WALL, bool NT, class S>
-__device__ __forceinline__ S aa_load(const Slots<S>& f, uint32_t nb, const Nav& v, int i, bool odd)
+template <class L, bool WALL, bool NT, class S, bool PAIRED>
+__device__ __forceinline__ S aa_load(const Slots<S, PAIRED>& f, uint32_t nb, const Nav& v, int i, bool odd)
 {
     if (!odd) return buf_ld<NT, S>(f.rsrc(i), nb, f.soff(i));
     if (WALL && nav_solid<L>(v, i, -1)) return buf_ld<NT, S>(f.rsrc(i), nb, f.soff(i));  // reflected at a wall last step
@@ -1162,7 +1168,8 @@ __device__ __forceinline__ void moments_node(CDesc& cs, int x, int y, int z, boo
     const uint32_t n = (uint32_t)x + (uint32_t)cs.sx * ((uint32_t)y + (uint32_t)cs.ny * (uint32_t)z);
     const uint32_t nb = n * (uint32_t)sizeof(S);
     const Nav nv = make_nav(cs, x, y, z, (int)sizeof(S));
-    const Slots<S> hs = slots<S>(cs.h, cs.N), gs = slots<S>(cs.g, cs.N);
+    constexpr bool PAIRED = sizeof(S) != 4 || DIMV == 2;
+    const Slots<S, PAIRED> hs = slots<S, PAIRED>(cs.h, cs.N), gs = slots<S, PAIRED>(cs.g, cs.N);
     const CT hsc = cconst<CT>(cs.h_inv_scale, cs.f32.h_inv_scale), gsc = cconst<CT>(cs.g_inv_scale, cs.f32.g_inv_scale);
     // 2-byte storage holds the populations less shifts made of phi (h) and
     // u (g) of this node one step earlier
