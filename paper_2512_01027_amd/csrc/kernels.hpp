@@ -1,7 +1,7 @@
 // Kernels of the coupled phase-field + P-u lattice Boltzmann step
 // (Otomo et al., arXiv 2512.01027, Sec. II) for gfx950.
 //
-// One time step is four launches over every resident case:
+// One time step is up to four launches over every resident case:
 //   k_moments  per node, no halo: gathers h and g (AA pattern) and writes
 //              phi = sum h, u* = sum g c, P* = rho_ref T sum g (the pressure
 //              the populations carry; the stored rest population lacks the
@@ -1495,9 +1495,11 @@ __global__ __launch_bounds__(256) void k_velocity(CaseTab cases, const int* hdr,
 // slides a 3x3x3 window up its column, which reads 13.5 cells a node from LDS
 // instead of 27 (186 and 104 instructions).  The arithmetic of a node is
 // k_pressure's and k_velocity's, term by term.  512x256x256 dam break:
-// pressure 313 -> 238 us (3.4 TB/s; its FP64 sums and 12 LDS words a cell keep
-// it from the copy's 6.3), velocity 227 -> 185 us (5.8 TB/s).  LDS and registers
-// hold 4 (pressure) and 5 (velocity) workgroups per CU; pressure at 3: 264 us.
+// pressure 313 -> 241 us (3.8 TB/s; its FP64 sums and 12 LDS words a cell keep
+// it from the copy's 6.3), velocity 227 -> 179 us (6.0 TB/s).  LDS and registers
+// hold 4 workgroups per CU in pressure (at 3: 264 us) and registers 6 in velocity.
+// Pressure on D3Q27 hydro takes all 128 registers of its 4 waves and spills one
+// on the wall path: 4.2 instead of 4.0 bytes written a node there.
 
 // f of a value, or of each element of a vector of them.
 template <class T, class F> __device__ __forceinline__ T each(T v, F f)
@@ -1796,8 +1798,8 @@ __device__ __forceinline__ void tile_gradients(const C& cells, typename C::At kb
     // The reads of a pair are issued AHEAD pairs before its sums, and no
     // sooner: the sums are pinned in order and the reads' address depends on
     // the last pin.  Left to itself the compiler issues all 26 neighbours'
-    // reads first, which alone takes 130 registers (the D3Q27 collide then
-    // needs 153-168; with 2 pairs ahead 83 on even and 115 on odd steps; 1 pair
+    // reads first, which alone takes 130 registers (the FP16 D3Q27 collide then
+    // needs 153-168; with 2 pairs ahead 75 on even and 106 on odd steps; 1 pair
     // ahead is 1-5% slower, 3 and more no faster).
     constexpr int AHEAD = 2, NP = G::Q / 2;
     CT qp[AHEAD][F::NF], qm[AHEAD][F::NF];
@@ -2086,7 +2088,7 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCe
     // stores stream past L2 on even steps (FP32 even collide 3% faster); on
     // odd steps, shifted by one node in x, each line is written partly by
     // this tile and partly by its x neighbour, and kept in L2 the parts merge
-    // (measured, FP16: the odd steps' writes 123 -> 92 B/node)
+    // (512 x 256 x 256, FP16: the odd steps' writes 123 streamed, 97 B/node kept)
     constexpr bool nts = PAR == 0 && nt_access<S, kStoreCollide>();
     const Slots<S> hs = slots<S>(cs.h, cs.N), gs = slots<S>(cs.g, cs.N);
     // own-node loads first
@@ -2365,15 +2367,15 @@ __device__ __forceinline__ void collide_tile(CDesc& cs, const TileCtx& t, TileCe
 }
 
 // Occupancy of the collision kernel: what bounds it in 2-byte storage is the
-// issue of vector instructions (about 1000 per wave) and the latency of its
+// issue of vector instructions (about 1100 per wave) and the latency of its
 // loads, so it wants waves.  The least number of waves per SIMD is set here;
 // registers (tile_gradients) and LDS (h kept in registers, no u-rebuild halo
-// on lattice sets that never use it) allow 5 on even and 4 on odd steps in
-// 2-byte storage, 4 in 4-byte and 2 in 8-byte storage.  Against 3, 3 and 1
-// before (512x256x256 dam break, FP16, even / odd step: 1.46 / 1.75 -> 1.09 /
-// 1.47 ms; 101x53x45 FP64: 58 -> 45 us).  Held to 3 waves by LDS the FP16
-// collide takes 1.50 ms on average; asked for 5 waves on odd steps it spills
-// (1.57 ms).
+// on lattice sets that never use it) allow on D3Q27 6 on even and 4 on odd steps
+// in FP16, 4 in BF16 and in 4-byte storage (by LDS; 3 where collide_lds_3d says
+// so) and 2 in 8-byte storage (by LDS).  Against 3, 3 and 1 before (512x256x256
+// dam break, FP16, even / odd step: 1.46 / 1.75 -> 1.11 / 1.49 ms; 101x53x45
+// FP64: 58 -> 45 us).  Held to 3 waves by LDS the FP16 collide takes 1.50 ms on
+// average; asked for 5 waves on odd steps it spills (1.57 ms).
 // (D3Q19 hydro in 4- and 8-byte storage: 3 and 1, by the LDS of the u rebuild.)
 template <int LS, class S> constexpr int collide_waves()
 {
