@@ -1903,8 +1903,8 @@ template <class S> struct Flow2D {
 // a CU's LDS then holds 3 workgroups with a fused case and 5 without; with room
 // for both in every launch it held 2 (step, before / after: 1024^2 104 / 96 us,
 // with walls 109 / 99, with a block 118 / 111; serving 12 of 200 x 400 with walls
-// 137 / 120, with a block each 143 / 128; a batch that mixes both kinds 153 /
-// 139).  The other storage widths held 5 and more: the same within 2%.
+// 137 / 120, with a block each 143 / 127; a batch that mixes both kinds 153 /
+// 137).  The other storage widths held 5 and more: the same within 2%.
 template <class S> constexpr int collide_lds_2d(bool fused)
 {
     const int h = sizeof(S) == 2 ? 0 : (int)sizeof(S) * D2Q9::Q * 256;
