@@ -44,8 +44,8 @@ def _image_fields(c, store):
     head = 8 + 8 + C.sizeof(B.Params) + 8 + 3 * 8
     aux = np.frombuffer(blob, dtype=at, offset=head + 18 * N * sb)
     assert aux.size == 4 * N
-    rows = aux.reshape(4, ny, -1)[:, :, :nx].astype(np.float64)
-    return rows[0], rows[2:]
+    rows = aux.reshape(4, ny, -1)[:, :, :nx]
+    return rows[0], rows[2:]  # (u is not kept up in 4- and 8-byte storage)
 
 
 @pytest.mark.parametrize("store", STORES)
